@@ -136,6 +136,8 @@ struct AlignParams {
     int32_t hard_share;         // percent of window workers that start on the hard queue
     int32_t route;              // search: append finished pairs to the window lists
     int32_t compact;            // window kernel: compact 16-lane groups (32-bit table slices)
+    int32_t pair_lanes;         // one pair per lane: lanes of a wavefront that take a pair
+    int32_t search_parts_log;   // one search part per lane: log2 of a pair's parts
     // Optional per-pair layout (serving: sequences sit anywhere in a device pool).
     const uint32_t* read_len;   // if set, pair i's read is [read_off[i], read_off[i] + read_len[i])
     const uint32_t* ref_len;
@@ -256,6 +258,13 @@ hipError_t launch_windows(const AlignParams& p, int blocks, hipStream_t s);
 // hit was taken by exactly one worker (batched form: `queued` = 1) and marks
 // each pair with an audit bit GENASM_FLAG_INTERNAL in its result.
 hipError_t launch_audit(const AlignParams& p, int queued, hipStream_t s);
+// The one-pair-per-lane path (lanes.h): planes of both streams and cleared
+// search keys, the start search, the windows (max_blocks workgroups at most, 0
+// = one per p.pair_lanes pairs; *n_blocks receives their number).
+constexpr int kLanePathCommit = 40;  // its windows commit at most this many bases (W - O)
+hipError_t launch_lane_prep(const AlignParams& p, uint64_t n_read, uint64_t n_ref, hipStream_t s);
+hipError_t launch_search_lane(const AlignParams& p, hipStream_t s);
+hipError_t launch_windows_lane(const AlignParams& p, uint64_t max_blocks, int* n_blocks, hipStream_t s);
 // Window workgroups one compute unit holds at once (registers and LDS), 0 on error.
 int windows_blocks_per_cu(const AlignParams& p);
 hipError_t launch_pack(const char* ascii, uint64_t n, uint8_t* packed, uint32_t* bad,

@@ -2568,6 +2568,8 @@ __global__ void k_audit(AlignParams P, int queued) {
     P.audit[pair] = a;
 }
 
+#include "lanes.h"
+
 // Copies each pair's CIGAR elements to dst + dst_off[pair] (one block per pair).
 __global__ void k_compact(const genasm_result* out, const uint64_t* dst_off, uint64_t n_pairs,
                           const uint32_t* cigar, uint32_t* dst) {
@@ -2646,6 +2648,32 @@ hipError_t launch_search_items(const AlignParams& p, uint32_t max_pairs, hipStre
 hipError_t launch_search_finalize(const AlignParams& p, uint32_t max_pairs, hipStream_t s) {
     if (max_pairs == 0) return hipSuccess;
     hipLaunchKernelGGL(k_search_finalize, dim3((max_pairs + 255) / 256), dim3(256), 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_lane_prep(const AlignParams& p, uint64_t n_read, uint64_t n_ref, hipStream_t s) {
+    const uint64_t rw = plane_words(n_read), fw = plane_words(n_ref);
+    const uint64_t threads = rw + fw > p.n_pairs ? rw + fw : p.n_pairs;
+    hipLaunchKernelGGL(k_lane_prep, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, p.reads,
+                       p.read_off, n_read, const_cast<u64*>(p.read_lo), const_cast<u64*>(p.read_hi), rw,
+                       p.refs, p.ref_off, n_ref, const_cast<u64*>(p.ref_lo), const_cast<u64*>(p.ref_hi),
+                       fw, p.search_key, p.n_pairs);
+    return hipGetLastError();
+}
+
+hipError_t launch_search_lane(const AlignParams& p, hipStream_t s) {
+    const uint64_t threads = p.n_pairs << p.search_parts_log;
+    hipLaunchKernelGGL(k_search_lane, dim3((unsigned)((threads + 63) / 64)), dim3(64), 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_windows_lane(const AlignParams& p, uint64_t max_blocks, int* n_blocks, hipStream_t s) {
+    const uint64_t want = (p.n_pairs + p.pair_lanes - 1) / p.pair_lanes;
+    const unsigned blocks = (unsigned)(max_blocks && want > max_blocks ? max_blocks : want);
+    const dim3 grid(blocks), block(128);
+    *n_blocks = (int)blocks;
+    if (p.stats) hipLaunchKernelGGL((k_windows_lane<true, false>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((k_windows_lane<false, false>), grid, block, 0, s, p);
     return hipGetLastError();
 }
 

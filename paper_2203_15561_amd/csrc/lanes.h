@@ -1,0 +1,489 @@
+// Kernels that take one pair per lane: the start search and the windows, on
+// vertical differences (diff_window.h).
+#pragma once
+
+#include "diff_window.h"
+
+static_assert(kLaneCols == kLanePathCommit, "the launch rule and the kernels agree");
+
+// ---------------------------------------------------------------------------
+// Windows
+// ---------------------------------------------------------------------------
+
+// The run-length CIGAR of a pair: the open run, and the runs already written.
+struct RunOut {
+    int cur_op;        // -1 before the pair's first op
+    uint32_t cur_len, written, room;
+    uint32_t* at;      // the pair's elements
+    bool overflow;
+};
+
+__device__ __forceinline__ void close_run(RunOut& r) {
+    if (r.written < r.room) r.at[r.written] = (r.cur_len << 2) | (uint32_t)r.cur_op;
+    else r.overflow = true;
+    ++r.written;
+}
+
+__device__ __forceinline__ void append_run(RunOut& r, int op, uint32_t len) {
+    if (len == 0u) return;
+    if (op != r.cur_op) {
+        if (r.cur_op >= 0) close_run(r);
+        r.cur_op = op;
+        r.cur_len = 0u;
+    }
+    r.cur_len += len;
+}
+
+// Appends a window's path to the pair's runs, a run of matches and the run of
+// edits after it at a time; closed runs go to device memory. Within a window a
+// deletion is never next to an insertion or before a substitution (the earlier
+// of the two edges in the order S, I, D would have been valid a cell before),
+// so the next event in the read and the next in the text are never at the same
+// cell.
+__device__ __forceinline__ void append_path(u64 ins, u64 sub, u64 del, int j, int i, RunOut& r) {
+    for (int it = 0; it < 2 * kLaneCols + 2 && (i | j) != 0; ++it) {  // i, j: bases left
+        const int k = min(ctz64(ins | sub | del), j);
+        ins >>= k;
+        sub >>= k;
+        del >>= k;
+        i -= k;
+        j -= k;
+        append_run(r, (int)GENASM_OP_MATCH, (uint32_t)k);
+        const uint32_t dl = (uint32_t)del, nl = (uint32_t)ins, sl = (uint32_t)sub;
+        const bool d = dl & 1u, n = nl & 1u, x = sl & 1u;
+        // the run of that edit; one of more than 31 takes another turn
+        const uint32_t stop = (d ? ~dl : n ? ~nl : x ? ~sl | dl : 1u) | 0x80000000u;
+        const int run = __builtin_ctz(stop);
+        const int dj = d ? 0 : run, di = !d && n ? 0 : run;
+        ins >>= dj;
+        sub >>= dj;
+        del >>= di;
+        j -= dj;
+        i -= di;
+        append_run(r, d ? (int)GENASM_OP_DEL : n ? (int)GENASM_OP_INS : (int)GENASM_OP_MISMATCH,
+                   (uint32_t)run);
+    }
+}
+
+// A window handed from the wavefront that computes it to the one that writes
+// its CIGAR: its path, and i_end, j_end << 8 and kMail* bits.
+constexpr uint32_t kMailWindow = 1u << 16;    // the lane computed a window
+constexpr uint32_t kMailFailed = 1u << 17;    // it has no solution within K (no path)
+constexpr uint32_t kMailInternal = 1u << 18;  // it committed nothing (never expected)
+constexpr uint32_t kMailEnd = 1u << 19;       // the pair's last window
+constexpr uint32_t kMailPark = 1u << 20;      // serving: the pair's turn ends
+constexpr uint32_t kMailHot = 1u << 21;       // serving: it advanced one window only
+struct LaneMail {
+    u64 ins[2][64], sub[2][64], del[2][64];
+    uint32_t info[2][64];
+    int32_t col[64];     // the pair's start column, -1: no window work
+    uint32_t pair[64];
+    uint32_t more[2];
+};
+
+// A lane's pairs: lane l of workgroup b takes list position b * lanes + l, then
+// every gridDim * lanes further on. Serving: the resident pairs, those that
+// advanced least first; otherwise all pairs, longest reads first if ordered.
+struct LaneShare {
+    uint64_t n, stride, first;
+    uint32_t n_hot;
+    int lanes;
+};
+template <bool SERVE>
+__device__ __forceinline__ LaneShare lane_share(const AlignParams& P) {
+    LaneShare s;
+    s.n_hot = 0;
+    if constexpr (SERVE) {
+        s.n_hot = __hip_atomic_load(P.counters + kCounterEasyLen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s.n = s.n_hot + (uint64_t)__hip_atomic_load(P.counters + kCounterHardLen, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_AGENT);
+        // spread over the whole grid
+        s.lanes = (int)max((uint64_t)1, min((uint64_t)64, (s.n + gridDim.x - 1) / gridDim.x));
+    } else {
+        s.n = P.n_pairs;
+        s.lanes = P.pair_lanes;
+    }
+    s.stride = (uint64_t)gridDim.x * s.lanes;
+    s.first = (uint64_t)blockIdx.x * s.lanes;
+    return s;
+}
+
+// The wavefront that computes the windows.
+template <bool STATS, bool SERVE>
+__device__ __forceinline__ void windows_compute(const AlignParams& P, LaneMail& mail, int lane) {
+    const LaneShare share = lane_share<SERVE>(P);
+    const uint64_t rorg = P.planes_from_off0 ? (P.read_off[0] & ~63ull) : 0;
+    const uint64_t forg = P.planes_from_off0 ? (P.ref_off[0] & ~63ull) : 0;
+    TurnClock turn;
+    if constexpr (SERVE) turn.open(P);
+    int buf = 0;
+    for (uint64_t first = share.first; first < share.n; first += share.stride) {
+        const uint64_t at = first + lane;
+        bool have = lane < share.lanes && at < share.n;
+        uint64_t pair = 0;
+        PairState st = fresh_state(0);
+        int col = -1;
+        if (have) {
+            if constexpr (SERVE) {
+                pair = at < share.n_hot ? P.easy_list[at] : P.hard_list[at - share.n_hot];
+                const SearchOut so = P.search[pair];
+                st = P.state[pair];
+                have = so.row >= 0 && !(st.flags & kStateDone);
+                if (have) {
+                    col = (int)so.col;
+                    if (!(st.flags & kStateStarted)) st = fresh_state(col);
+                }
+            } else {
+                pair = P.order ? P.order[at] : at;
+                have = search_outcome(P, pair) >= 0;
+                if (have) {
+                    col = (int)P.search[pair].col;
+                    st = fresh_state(col);
+                }
+            }
+        }
+        mail.col[lane] = col;
+        mail.pair[lane] = (uint32_t)pair;
+        PairCursor pc{0, 0, 0, 0, 0, 0};
+        SeqCursor rc{}, fc{};
+        uint32_t max_windows = 0, done_here = 0;
+        u64 pl = 0, ph = 0, tl = 0, th = 0;
+        if (have) {
+#if defined(GENASM_DEBUG)
+            if (P.audit) atomicAdd(P.audit + pair, kAuditTake);  // queue audit
+#endif
+            pc = pair_cursor(P, pair);
+            max_windows = (uint32_t)pc.m + (uint32_t)pc.n + 1u;
+            const uint64_t rb = pc.rb - rorg + st.pj, fb = pc.fb - forg + st.ti;
+            seq_open(rc, P.read_lo, P.read_hi, rb);
+            seq_open(fc, P.ref_lo, P.ref_hi, fb);
+            seq_window(rc, P.read_lo, P.read_hi, rb, pl, ph);
+            seq_window(fc, P.ref_lo, P.ref_hi, fb, tl, th);
+        }
+        u64 st_wops = 0, st_cells = 0, st_table = 0, st_tb = 0, st_steps = 0, cyc_dc = 0;
+        u64 cyc_start = 0, wall_start = 0;
+        if constexpr (STATS) {
+            cyc_start = clock64();
+            wall_start = wall_clock64();
+        }
+        bool any = true;
+        while (any) {
+            const int mw = have ? min(P.W, pc.m - st.pj) : 64;
+            const int nw = have ? min(P.W, pc.n - st.ti) : 64;
+            u64 cyc0 = 0;
+            if constexpr (STATS) cyc0 = clock64();
+            const bool ragged = __ballot(mw < 64 || nw < 64) != 0ull;
+            const WindowPath w = ragged ? window_path<true>(pl, ph, tl, th, mw, nw, P.L)
+                                        : window_path<false>(pl, ph, tl, th, mw, nw, P.L);
+            bool over = false;
+            if constexpr (SERVE) over = turn.active && turn.over();
+            uint32_t info = 0u;
+            if (have) {
+                if constexpr (STATS) st_cells += (u64)mw * nw;
+                info = kMailWindow | (uint32_t)w.i_end | ((uint32_t)w.j_end << 8);
+                ++st.nwin;
+                ++done_here;
+                // every window commits at least one base, so a pair has at most m + n
+                if (st.nwin > max_windows || w.i_end + w.j_end == 0) info |= kMailInternal | kMailFailed;
+                else if (w.dist > P.K) info |= kMailFailed;
+                if (info & kMailFailed) {
+                    info |= kMailEnd;
+                } else {
+                    st.ti += w.i_end;
+                    st.pj += w.j_end;
+                    if (st.pj >= pc.m) {
+                        info |= kMailEnd;
+                    } else {
+                        seq_window(rc, P.read_lo, P.read_hi, pc.rb - rorg + st.pj, pl, ph);
+                        seq_window(fc, P.ref_lo, P.ref_hi, pc.fb - forg + st.ti, tl, th);
+                    }
+                    if constexpr (STATS) {
+                        st_wops += (u64)nw * (2 + 6 * w.dist);
+                        st_table += (u64)(w.dist + 1) * (min(nw, P.L) + 1);
+                        st_tb += 2u * (__builtin_popcountll(w.ins) + __builtin_popcountll(w.sub) +
+                                       __builtin_popcountll(w.del));
+                        st_steps += (u64)nw;
+                        cyc_dc += clock64() - cyc0;
+                    }
+                }
+                if constexpr (SERVE) {
+                    // every pair advances at least one window per launch; none starts
+                    // once its turn has ended
+                    if (!(info & kMailEnd) &&
+                        (over || (P.window_budget != 0u && done_here >= P.window_budget)))
+                        info |= kMailPark | (done_here <= 1u ? kMailHot : 0u);
+                    if (info & (kMailEnd | kMailPark)) {
+                        PairState* ps = P.state + pair;
+                        ps->ti = st.ti;
+                        ps->pj = st.pj;
+                        ps->nwin = st.nwin;
+                    }
+                }
+                if (info & (kMailEnd | kMailPark)) {
+                    have = false;
+                    if constexpr (STATS) {
+                        u64* stp = P.stats + pair * kStatCount;
+                        stp[kStatWindowWordOps] += st_wops;
+                        stp[kStatWindowCells] += st_cells;
+                        stp[kStatTableWords] += st_table;
+                        stp[kStatTbReads] += st_tb;
+                        stp[kStatWindowLaneSteps] += st_steps;
+                        stp[kStatWindows] += done_here;
+                        stp[kStatDcCycles] += cyc_dc;
+                        stp[kStatPairCycles] += clock64() - cyc_start;
+                        if (!stp[kStatPairStart]) stp[kStatPairStart] = wall_start;
+                        stp[kStatPairEnd] = wall_clock64();
+                    }
+                }
+            }
+            mail.ins[buf][lane] = w.ins;
+            mail.sub[buf][lane] = w.sub;
+            mail.del[buf][lane] = w.del;
+            mail.info[buf][lane] = info;
+            any = __ballot(have) != 0ull;
+            if (lane == 0) mail.more[buf] = any ? 1u : 0u;
+            buf ^= 1;
+            __syncthreads();
+        }
+    }
+}
+
+// The wavefront that writes the CIGARs and results, a window behind the other.
+template <bool STATS, bool SERVE>
+__device__ __forceinline__ void windows_write(const AlignParams& P, const LaneMail& mail, int lane) {
+    const LaneShare share = lane_share<SERVE>(P);
+    int buf = 0;
+    for (uint64_t first = share.first; first < share.n; first += share.stride) {
+        bool more = true, opened = false;
+        uint64_t pair = 0, base = 0;
+        PairState st = fresh_state(0);
+        RunOut run{-1, 0u, 0u, 0u, nullptr, false};
+        int col = -1;
+        u64 cyc_tb = 0;
+        while (more) {
+            __syncthreads();
+            if (!opened) {
+                opened = true;
+                col = mail.col[lane];
+                pair = mail.pair[lane];
+                if (col >= 0) {
+                    const PairCursor pc = pair_cursor(P, pair);
+                    base = pair_run_base(P, pair);
+                    const uint64_t limit = min(P.cigar_cap, base + (uint64_t)pc.m + (uint64_t)pc.n);
+                    st = fresh_state(col);
+                    if constexpr (SERVE) {
+                        // the other wavefront may already be writing ti, pj and nwin
+                        const PairState* ps = P.state + pair;
+                        if (ps->flags & kStateStarted) {
+                            st.score = ps->score;
+                            st.written = ps->written;
+                            st.cur_op = ps->cur_op;
+                            st.cur_len = ps->cur_len;
+                            st.flags = ps->flags;
+                        }
+                    }
+                    run = RunOut{st.cur_op, st.cur_len, st.written,
+                                 (uint32_t)(limit > base ? limit - base : 0ull), P.cigar + base,
+                                 (st.flags & kStateOverflow) != 0};
+                }
+            }
+            more = mail.more[buf] != 0u;
+            const uint32_t info = mail.info[buf][lane];
+            const u64 cyc0 = STATS ? clock64() : 0ull;
+            if (info & kMailWindow) {
+                if (!(info & kMailFailed)) {
+                    const u64 ins = mail.ins[buf][lane], sub = mail.sub[buf][lane], del = mail.del[buf][lane];
+                    st.score += __builtin_popcountll(ins) + __builtin_popcountll(sub) +
+                                __builtin_popcountll(del);
+                    append_path(ins, sub, del, (int)((info >> 8) & 0xFFu), (int)(info & 0xFFu), run);
+                    st.ti += (int)(info & 0xFFu);
+                }
+                ++st.nwin;
+                if constexpr (STATS) cyc_tb += clock64() - cyc0;
+                const bool failed = (info & kMailFailed) != 0u;
+                if (info & kMailEnd) {
+                    if (!failed && run.cur_op >= 0) close_run(run);
+                    genasm_result r;
+                    int end = st.ti;
+                    uint32_t nwin = st.nwin;
+                    if constexpr (SERVE) {
+                        end = P.state[pair].ti;
+                        nwin = P.state[pair].nwin;
+                    }
+                    r.edit_distance = failed ? -1 : st.score;
+                    r.ref_begin = failed ? 0u : (uint32_t)col;
+                    r.ref_end = failed ? 0u : (uint32_t)end;
+                    r.cigar_len = failed || run.overflow ? 0u : run.written;
+                    r.n_windows = nwin;
+                    r.cigar_off = base;
+                    r.flags = (run.overflow && !failed ? GENASM_FLAG_CIGAR_OVERFLOW : 0u) |
+                              (info & kMailInternal ? GENASM_FLAG_INTERNAL : 0u);
+                    P.out[pair] = r;
+                    if constexpr (STATS) P.stats[pair * kStatCount + kStatTbCycles] += cyc_tb;
+                }
+                if constexpr (SERVE) {
+                    if (info & (kMailEnd | kMailPark)) {
+                        PairState* ps = P.state + pair;
+                        ps->score = st.score;
+                        ps->written = run.written;
+                        ps->cur_op = run.cur_op;
+                        ps->cur_len = run.cur_len;
+                        ps->flags = st.flags | (run.overflow ? kStateOverflow : 0u) |
+                                    (failed ? kStateFailed : 0u) |
+                                    (info & kMailInternal ? kStateInternal : 0u) |
+                                    (info & kMailEnd ? kStateDone : 0u);
+                    }
+                }
+            }
+            if constexpr (SERVE) {
+                // the finished list, or the pair's list for the next iteration
+                const bool fin = (info & kMailEnd) != 0u;
+                const bool hot = (info & kMailPark) && (info & kMailHot);
+                const bool cold = (info & kMailPark) && !(info & kMailHot);
+                if (P.fin_list && __ballot(fin || hot || cold) != 0ull) {
+                    const uint32_t pf = wave_append(P.fin_len, fin);
+                    if (fin) P.fin_list[pf] = (uint32_t)pair;
+                    const uint32_t p1 = wave_append(P.next_len + kCounterEasyLen, hot);
+                    if (hot) P.next_hot[p1] = (uint32_t)pair;
+                    const uint32_t p2 = wave_append(P.next_len + kCounterHardLen, cold);
+                    if (cold) P.next_cold[p2] = (uint32_t)pair;
+                }
+            }
+            buf ^= 1;
+        }
+    }
+}
+
+// Window kernel, two wavefronts per workgroup and one pair per lane of them:
+// one computes the windows, the other turns each window's path into CIGAR runs
+// while the next window is computed.
+template <bool STATS, bool SERVE>
+__global__ __launch_bounds__(128, 2) void k_windows_lane(AlignParams P) {
+    __shared__ LaneMail mail;
+    const int lane = threadIdx.x & 63;
+    if (threadIdx.x < 64) windows_compute<STATS, SERVE>(P, mail, lane);
+    else windows_write<STATS, SERVE>(P, mail, lane);
+}
+
+// ---------------------------------------------------------------------------
+// Start search
+// ---------------------------------------------------------------------------
+
+// Lane t searches part t mod `parts` of pair t / parts (parts a power of two):
+// `cols` output columns (a multiple of 64) from part * cols on, in blocks of 64
+// columns from the right. E over the first read window's m1 bases at a column
+// within m1 + m1 columns of the text end depends on no column further right
+// (an alignment of at most m1 edits reaches at most 2 m1 text bases), so a part
+// starts 128 columns past its last output column. Columns it computes past its
+// own are never below their true value, so they need no check; columns past
+// the reference match nothing and stay at m1, which is no hit. The pair's key
+// (row << 32 | column) is the least over its parts: least row, then leftmost
+// column.
+template <bool RAGGED>
+__device__ __forceinline__ uint32_t search_block(DiffColumn& c, int& score, u64 a, u64 b, u64 pad,
+                                                 const TextBlock& text) {
+    uint32_t best = ~0u;
+#pragma unroll
+    for (int i = 63; i >= 0; --i) {
+        u64 out;
+        const u64 Eq = equal_rows<RAGGED>(a, b, pad, text, i, out);
+        u64 D0, Ph, Mh;
+        diff_step(c, Eq, D0, Ph, Mh);
+        score += (int)((uint32_t)(Ph >> 32) >> 31) + ((int32_t)(uint32_t)(Mh >> 32) >> 31);
+        best = min(best, ((uint32_t)score << 6) + (uint32_t)i);
+    }
+    return best;
+}
+
+__global__ __launch_bounds__(64) void k_search_lane(AlignParams P) {
+    const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t at = t >> P.search_parts_log;
+    const uint32_t part = (uint32_t)(t & ((1ull << P.search_parts_log) - 1));
+    bool have = at < P.n_pairs;
+    uint64_t pair = 0;
+    PairCursor pc{0, 0, 0, 0, 0, 0};
+    int c0 = 0, nb = 0, m1 = 0, e = 0;
+    if (have) {
+        pair = P.order ? P.order[at] : at;
+        pc = pair_cursor(P, pair);
+        const uint64_t per = (((uint64_t)pc.n + (1ull << P.search_parts_log) - 1) >> P.search_parts_log);
+        const uint64_t cols = max((uint64_t)64, (per + 63) & ~63ull);
+        have = pc.m > 0 && (uint64_t)part * cols < (uint64_t)pc.n;
+        if (have) {
+            m1 = min(P.W, pc.m);
+            c0 = (int)(part * cols);
+            e = (int)min((uint64_t)pc.n, (uint64_t)c0 + cols + 128);
+            nb = (e - c0 + 63) / 64;
+        }
+    }
+    if (__ballot(have) == 0ull) return;
+    const uint64_t rorg = P.planes_from_off0 ? (P.read_off[0] & ~63ull) : 0;
+    const uint64_t forg = P.planes_from_off0 ? (P.ref_off[0] & ~63ull) : 0;
+    u64 a = 0, b = 0, pad = 0;
+    u64 lo1 = 0, hi1 = 0, lo0 = 0, hi0 = 0;  // words q + 1 and q of the block's text
+    const uint64_t bit0 = pc.fb - forg + (uint64_t)c0;
+    const int sh = (int)(bit0 & 63);
+    uint64_t q = (bit0 >> 6) + (uint64_t)(nb > 0 ? nb - 1 : 0);
+    if (have) {
+        SeqCursor rc;
+        u64 pl, ph;
+        seq_open(rc, P.read_lo, P.read_hi, pc.rb - rorg);
+        seq_window(rc, P.read_lo, P.read_hi, pc.rb - rorg, pl, ph);
+        a = __builtin_bitreverse64(pl);
+        b = __builtin_bitreverse64(ph);
+        pad = m1 < 64 ? (1ull << (64 - m1)) - 1 : 0ull;
+        lo1 = P.ref_lo[q + 1];
+        hi1 = P.ref_hi[q + 1];
+        lo0 = P.ref_lo[q];
+        hi0 = P.ref_hi[q];
+    }
+    DiffColumn c{~pad, 0ull};
+    int score = m1;
+    u64 key = ~0ull;
+    bool active = have;
+    while (__ballot(active) != 0ull) {
+        const u64 tl = funnel64(lo0, lo1, sh), th = funnel64(hi0, hi1, sh);
+        lo1 = lo0;
+        hi1 = hi0;
+        const int col = c0 + 64 * (nb - 1);
+        if (active && nb > 1) {  // the next block's words
+            --q;
+            lo0 = P.ref_lo[q];
+            hi0 = P.ref_hi[q];
+        }
+        const int left = e - col;  // valid columns of the block
+        const u64 past = left < 64 ? ~0ull << max(left, 0) : 0ull;
+        const bool ragged = __ballot(active && (left < 64 || m1 < 64)) != 0ull;
+        const uint32_t k = ragged ? search_block<true>(c, score, a, b, pad, text_block(tl, th, past))
+                                  : search_block<false>(c, score, a, b, 0ull, text_block(tl, th, 0ull));
+        if (active) {
+            const u64 cand = ((u64)(k >> 6) << 32) | (u64)(uint32_t)(col + (int)(k & 63u));
+            key = min(key, cand);
+            --nb;
+            active = nb > 0;
+        }
+    }
+    if (!have) return;
+    const int Kr = min(P.K, m1 - 1);
+    if ((int)(key >> 32) <= Kr) atomicMin(P.search_key + pair, key);
+    if (P.stats) atomicAdd(P.stats + pair * kStatCount + kStatSearchLaneSteps, (u64)(e - c0));
+}
+
+// ---------------------------------------------------------------------------
+// Launchers
+// ---------------------------------------------------------------------------
+
+__global__ void k_lane_prep(const uint8_t* reads, const uint64_t* d_read, uint64_t n_read, u64* rlo,
+                            u64* rhi, uint64_t rw, const uint8_t* refs, const uint64_t* d_ref,
+                            uint64_t n_ref, u64* flo, u64* fhi, uint64_t fw, u64* key, uint64_t n_pairs) {
+    const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < n_pairs) key[t] = ~0ull;
+    const bool rd = t < rw;
+    const uint64_t w = rd ? t : t - rw;
+    if (!rd && w >= fw) return;
+    const uint64_t b0 = rd ? d_read[0] : d_ref[0];
+    u64 x, y;
+    plane_word(rd ? reads : refs, (b0 + (rd ? n_read : n_ref) + 3) / 4, (b0 >> 6) + w, x, y);
+    (rd ? rlo : flo)[w] = x;
+    (rd ? rhi : fhi)[w] = y;
+}

@@ -372,6 +372,72 @@ int genasm_pack_dev(genasm_ctx* ctx, const char* d_ascii, uint64_t n, uint8_t* d
 
 namespace {
 
+// Whether a batched launch takes the one-pair-per-lane path (lanes.h): the
+// default geometry of the row-table kernels, which any other value of these
+// fields asks for, and windows that commit no more bases than the path keeps
+// columns for. At 20,000 pairs of 10 kb the start search and the windows take
+// 0.25 and 1.8 ms on it, 2.7 and 15.6 ms on the row tables; it is also the
+// faster one for 1,000 reads of 100 bases (0.07 against 0.10 ms) and for 67
+// reads of 30 kb (4.2 against 13.7 ms).
+bool lane_path(const genasm_launch& L, int commit) {
+    return L.group_lanes == 16 && L.search_lanes == 16 && L.lds_rows == 16 && L.hard_row == 16 &&
+           L.hard_lanes == 16 && L.tb_prefetch == 0 && L.hard_share == 50 && L.table_bits == 64 &&
+           L.search_per_cu == 8 && commit <= kLanePathCommit;
+}
+
+// The batched form on that path: planes and cleared search keys, the order,
+// the start search, the windows. Scratch comes from `carved` (enough for the
+// row-table layout, of which this takes a part) or from the context's buffer.
+template <class Mark>
+int align_lanes(genasm_ctx* ctx, AlignParams p, const genasm_launch& L, uint64_t total_read_bases,
+                uint64_t total_ref_bases, Carver* carved, Mark&& mark, hipStream_t s) {
+    uint32_t *hist = nullptr, *order = nullptr;
+    auto carve = [&](Carver& c) {
+        p.search = c.take<SearchOut>(p.n_pairs);
+        p.search_key = c.take<unsigned long long>(p.n_pairs);
+        hist = c.take<uint32_t>(kLptBuckets);
+        order = c.take<uint32_t>(p.n_pairs);
+    };
+    if (carved) {
+        carve(*carved);
+    } else {
+        Carver dry{nullptr};
+        carve(dry);
+        const int rc = ensure(ctx, &ctx->scratch, &ctx->scratch_cap, dry.off + 256);
+        if (rc) return rc;
+        Carver real{ctx->scratch};
+        carve(real);
+    }
+    // A pair's search parts: about 131,072 lanes (two wavefronts per SIMD), each
+    // part at least 512 columns of an average reference (128 more are computed
+    // for it).
+    const uint64_t mean = total_ref_bases / p.n_pairs;
+    while ((p.n_pairs << p.search_parts_log) < 131072 && (mean >> p.search_parts_log) > 512)
+        ++p.search_parts_log;
+    // Pairs per wavefront: as few as leave every SIMD one wavefront (a workgroup
+    // has two). A SIMD with one wavefront already issues at nine tenths of its
+    // rate, so sharing SIMDs costs time: 20,000 pairs of 10 kb take 1.8 ms 64 to
+    // a wavefront, 2.9 ms 32 to a wavefront.
+    p.pair_lanes = 1;
+    while (p.pair_lanes < 64 && (uint64_t)ctx->num_cus * 2 * p.pair_lanes < p.n_pairs) p.pair_lanes *= 2;
+    const uint64_t max_blocks = (uint64_t)ctx->num_cus * L.workers_per_cu;
+    CHECK_HIP(ctx, mark(0));
+    CHECK_HIP(ctx, launch_lane_prep(p, total_read_bases, total_ref_bases, s));
+    if (L.lpt_order) {
+        CHECK_HIP(ctx, launch_lpt_order(p.read_off, p.n_pairs, hist, order, s));
+        p.order = order;
+    }
+    CHECK_HIP(ctx, mark(1));
+    CHECK_HIP(ctx, launch_search_lane(p, s));
+    CHECK_HIP(ctx, mark(2));
+    int blocks = 0;
+    CHECK_HIP(ctx, launch_windows_lane(p, max_blocks, &blocks, s));
+    if (ctx->profiling) ctx->prof_window_blocks = blocks;
+    CHECK_HIP(ctx, launch_audit(p, 1, s));  // debug builds only
+    CHECK_HIP(ctx, mark(3));
+    return GENASM_OK;
+}
+
 // The device-form call. Scratch (bit planes, search lists, queues, table
 // spill, profiling counters) comes from the context's buffers, grown on
 // demand, or with `noalloc` from the static `scratch` array, in which case
@@ -528,6 +594,7 @@ int align_dev(genasm_ctx* ctx, const uint8_t* d_reads2b, const uint64_t* d_read_
     // more resident search workgroups than 8 per CU make smaller chunks (each
     // rescanning m1 + 64 columns past its end) and measured slower
     const int search_blocks = ctx->num_cus * L.search_per_cu;
+    const bool lanes = lane_path(L, p.L);
     const int spill_rows = p.compact ? kCompactSpillRows : 64 - L.lds_rows;
     // Search chunks: at least kBatchSearchChunk columns, and large enough that
     // the batch makes about two items per search group (counted at 8 search
@@ -562,6 +629,11 @@ int align_dev(genasm_ctx* ctx, const uint8_t* d_reads2b, const uint64_t* d_read_
         return dry.off + 256;
     };
     int per_cu = L.workers_per_cu;
+    if (lanes && !noalloc) {
+        // no spill, no item lists; the no-allocation call keeps the layout below, so
+        // that it takes the same batches as ever
+        return align_lanes(ctx, p, L, total_read_bases, total_ref_bases, nullptr, mark, s);
+    }
     if (per_cu == 0) {
         // as many as stay resident together (LDS and registers), so that no
         // workgroup of the persistent grid waits for another to finish; without
@@ -585,6 +657,7 @@ int align_dev(genasm_ctx* ctx, const uint8_t* d_reads2b, const uint64_t* d_read_
     if (profiling) ctx->prof_window_blocks = win_blocks;
     Carver real{base};
     real.off = base_off;
+    if (lanes) return align_lanes(ctx, p, L, total_read_bases, total_ref_bases, &real, mark, s);
     auto [items, hist, order] = carve(real, workers);
 
     CHECK_HIP(ctx, mark(0));
