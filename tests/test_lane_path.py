@@ -81,3 +81,20 @@ def test_one_read_against_a_long_reference():
         for r, at in zip(reads, want):
             res, cig = ctx.align([r], [ref], 5)
             assert (int(res["edit_distance"][0]), int(res["ref_begin"][0]), cig[0]) == (0, at, "50=")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("longest", [1, 64, 65, 128, 256, 257, 512, 513, 1024])
+def test_filter_at_its_edges(longest):
+    # a lane per 64 read bases: reads up to each lane count's limit, shorter
+    # ones whose last lanes have no rows, references around 0 and around blocks
+    # of 32 columns, k from 0 to past the read length
+    lens = sorted({m for m in (0, 1, 2, 40, 63, 64, 65, 127, 129, 255, 400, longest - 1, longest) if 0 <= m <= longest})
+    reads, refs = pairs_of(90, 40 + longest, lens, [longest + 9, 0, 1, 31, 32, 33, 64, 65, longest + 60])
+    with ga.Context(0) as ctx:
+        for k in (0, 12, 63):
+            dist, start = ctx.filter(reads, refs, k)
+            for i in range(len(reads)):
+                want = oracle.filter_pair(reads[i], refs[i], k)
+                got = (int(dist[i]), int(start[i]))
+                assert got == (want if want[0] >= 0 else (-1, 0)), (i, len(reads[i]), len(refs[i]), k, got, want)
