@@ -265,6 +265,10 @@ constexpr int kLanePathCommit = 40;  // its windows commit at most this many bas
 hipError_t launch_lane_prep(const AlignParams& p, uint64_t n_read, uint64_t n_ref, hipStream_t s);
 hipError_t launch_search_lane(const AlignParams& p, hipStream_t s);
 hipError_t launch_windows_lane(const AlignParams& p, uint64_t max_blocks, int* n_blocks, hipStream_t s);
+// The same for a serving iteration: the search over the items of
+// launch_search_items, and a turn of the resident pairs.
+hipError_t launch_search_lane_items(const AlignParams& p, int blocks, hipStream_t s);
+hipError_t launch_windows_serve(const AlignParams& p, int blocks, hipStream_t s);
 // Window workgroups one compute unit holds at once (registers and LDS), 0 on error.
 int windows_blocks_per_cu(const AlignParams& p);
 hipError_t launch_pack(const char* ascii, uint64_t n, uint8_t* packed, uint32_t* bad,
@@ -275,9 +279,11 @@ hipError_t launch_init_counters(uint32_t* counters, uint32_t n_pairs, hipStream_
 // the per-pair outcome and window routing.
 hipError_t launch_search_items(const AlignParams& p, uint32_t max_pairs, hipStream_t s);
 hipError_t launch_search_finalize(const AlignParams& p, uint32_t max_pairs, hipStream_t s);
-// Reference columns per start-search item: batched calls and the serving loop.
+// Reference columns per start-search item: batched calls and the serving loop,
+// there also with one item per lane.
 constexpr uint32_t kBatchSearchChunk = 4096;
 constexpr uint32_t kServeSearchChunk = 1024;
+constexpr uint32_t kServeLaneSearchChunk = 256;
 // Upper bound of the search items of a batch.
 inline uint64_t search_item_cap(uint64_t n_pairs, uint64_t total_ref_bases, uint32_t chunk) {
     return chunk ? n_pairs + total_ref_bases / chunk + 1 : n_pairs + 1;

@@ -2534,6 +2534,16 @@ hipError_t launch_search_lane(const AlignParams& p, hipStream_t s) {
     return hipGetLastError();
 }
 
+hipError_t launch_search_lane_items(const AlignParams& p, int blocks, hipStream_t s) {
+    hipLaunchKernelGGL(k_search_lane_items, dim3(blocks), dim3(64), 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_windows_serve(const AlignParams& p, int blocks, hipStream_t s) {
+    hipLaunchKernelGGL((k_windows_lane<false, true>), dim3(blocks), dim3(128), 0, s, p);
+    return hipGetLastError();
+}
+
 hipError_t launch_windows_lane(const AlignParams& p, uint64_t max_blocks, int* n_blocks, hipStream_t s) {
     const uint64_t want = (p.n_pairs + p.pair_lanes - 1) / p.pair_lanes;
     const unsigned blocks = (unsigned)(max_blocks && want > max_blocks ? max_blocks : want);

@@ -78,8 +78,23 @@ struct LaneMail {
     uint32_t info[2][64];
     int32_t col[64];     // the pair's start column, -1: no window work
     uint32_t pair[64];
+    int32_t ti[64];      // its text cursor and window count when the launch took it up
+    uint32_t nwin[64];
     uint32_t more[2];
 };
+
+// Workgroup barrier for what is handed over in LDS. The wavefronts share nothing
+// in device memory, so their loads and stores there stay in flight across it
+// (a __syncthreads would wait for the next window's words).
+__device__ __forceinline__ void mail_barrier() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+#else
+    __syncthreads();
+#endif
+}
 
 // A lane's pairs: lane l of workgroup b takes list position b * lanes + l, then
 // every gridDim * lanes further on. Serving: the resident pairs, those that
@@ -144,6 +159,8 @@ __device__ __forceinline__ void windows_compute(const AlignParams& P, LaneMail& 
         }
         mail.col[lane] = col;
         mail.pair[lane] = (uint32_t)pair;
+        mail.ti[lane] = st.ti;
+        mail.nwin[lane] = st.nwin;
         PairCursor pc{0, 0, 0, 0, 0, 0};
         SeqCursor rc{}, fc{};
         uint32_t max_windows = 0, done_here = 0;
@@ -243,7 +260,7 @@ __device__ __forceinline__ void windows_compute(const AlignParams& P, LaneMail& 
             any = __ballot(have) != 0ull;
             if (lane == 0) mail.more[buf] = any ? 1u : 0u;
             buf ^= 1;
-            __syncthreads();
+            mail_barrier();
         }
     }
 }
@@ -261,7 +278,7 @@ __device__ __forceinline__ void windows_write(const AlignParams& P, const LaneMa
         int col = -1;
         u64 cyc_tb = 0;
         while (more) {
-            __syncthreads();
+            mail_barrier();
             if (!opened) {
                 opened = true;
                 col = mail.col[lane];
@@ -272,7 +289,7 @@ __device__ __forceinline__ void windows_write(const AlignParams& P, const LaneMa
                     const uint64_t limit = min(P.cigar_cap, base + (uint64_t)pc.m + (uint64_t)pc.n);
                     st = fresh_state(col);
                     if constexpr (SERVE) {
-                        // the other wavefront may already be writing ti, pj and nwin
+                        // ti, pj and nwin are the other wavefront's to read and write
                         const PairState* ps = P.state + pair;
                         if (ps->flags & kStateStarted) {
                             st.score = ps->score;
@@ -282,6 +299,8 @@ __device__ __forceinline__ void windows_write(const AlignParams& P, const LaneMa
                             st.flags = ps->flags;
                         }
                     }
+                    st.ti = mail.ti[lane];
+                    st.nwin = mail.nwin[lane];
                     run = RunOut{st.cur_op, st.cur_len, st.written,
                                  (uint32_t)(limit > base ? limit - base : 0ull), P.cigar + base,
                                  (st.flags & kStateOverflow) != 0};
@@ -304,17 +323,11 @@ __device__ __forceinline__ void windows_write(const AlignParams& P, const LaneMa
                 if (info & kMailEnd) {
                     if (!failed && run.cur_op >= 0) close_run(run);
                     genasm_result r;
-                    int end = st.ti;
-                    uint32_t nwin = st.nwin;
-                    if constexpr (SERVE) {
-                        end = P.state[pair].ti;
-                        nwin = P.state[pair].nwin;
-                    }
                     r.edit_distance = failed ? -1 : st.score;
                     r.ref_begin = failed ? 0u : (uint32_t)col;
-                    r.ref_end = failed ? 0u : (uint32_t)end;
+                    r.ref_end = failed ? 0u : (uint32_t)st.ti;
                     r.cigar_len = failed || run.overflow ? 0u : run.written;
-                    r.n_windows = nwin;
+                    r.n_windows = st.nwin;
                     r.cigar_off = base;
                     r.flags = (run.overflow && !failed ? GENASM_FLAG_CIGAR_OVERFLOW : 0u) |
                               (info & kMailInternal ? GENASM_FLAG_INTERNAL : 0u);
@@ -395,28 +408,13 @@ __device__ __forceinline__ uint32_t search_block(DiffColumn& c, int& score, u64 
     return best;
 }
 
-__global__ __launch_bounds__(64) void k_search_lane(AlignParams P) {
-    const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const uint64_t at = t >> P.search_parts_log;
-    const uint32_t part = (uint32_t)(t & ((1ull << P.search_parts_log) - 1));
-    bool have = at < P.n_pairs;
-    uint64_t pair = 0;
-    PairCursor pc{0, 0, 0, 0, 0, 0};
-    int c0 = 0, nb = 0, m1 = 0, e = 0;
-    if (have) {
-        pair = P.order ? P.order[at] : at;
-        pc = pair_cursor(P, pair);
-        const uint64_t per = (((uint64_t)pc.n + (1ull << P.search_parts_log) - 1) >> P.search_parts_log);
-        const uint64_t cols = max((uint64_t)64, (per + 63) & ~63ull);
-        have = pc.m > 0 && (uint64_t)part * cols < (uint64_t)pc.n;
-        if (have) {
-            m1 = min(P.W, pc.m);
-            c0 = (int)(part * cols);
-            e = (int)min((uint64_t)pc.n, (uint64_t)c0 + cols + 128);
-            nb = (e - c0 + 63) / 64;
-        }
-    }
-    if (__ballot(have) == 0ull) return;
+// Searches output columns [c0, c0 + cols) of a pair (lanes without `have`: none)
+// and combines its least key. All lanes of the wavefront call this together.
+__device__ __forceinline__ void search_part(const AlignParams& P, bool have, uint64_t pair, const PairCursor& pc,
+                                            int c0, uint64_t cols) {
+    const int m1 = min(P.W, pc.m);
+    const int e = (int)min((uint64_t)pc.n, (uint64_t)c0 + cols + 128);
+    int nb = have ? (e - c0 + 63) / 64 : 0;
     const uint64_t rorg = P.planes_from_off0 ? (P.read_off[0] & ~63ull) : 0;
     const uint64_t forg = P.planes_from_off0 ? (P.ref_off[0] & ~63ull) : 0;
     u64 a = 0, b = 0, pad = 0;
@@ -464,9 +462,46 @@ __global__ __launch_bounds__(64) void k_search_lane(AlignParams P) {
         }
     }
     if (!have) return;
-    const int Kr = min(P.K, m1 - 1);
-    if ((int)(key >> 32) <= Kr) atomicMin(P.search_key + pair, key);
+    if ((int)(key >> 32) <= min(P.K, m1 - 1)) atomicMin(P.search_key + pair, key);
     if (P.stats) atomicAdd(P.stats + pair * kStatCount + kStatSearchLaneSteps, (u64)(e - c0));
+}
+
+__global__ __launch_bounds__(64) void k_search_lane(AlignParams P) {
+    const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t at = t >> P.search_parts_log;
+    const uint32_t part = (uint32_t)(t & ((1ull << P.search_parts_log) - 1));
+    bool have = at < P.n_pairs;
+    uint64_t pair = 0, cols = 64;
+    PairCursor pc{0, 0, 0, 0, 0, 0};
+    if (have) {
+        pair = P.order ? P.order[at] : at;
+        pc = pair_cursor(P, pair);
+        const uint64_t per = (((uint64_t)pc.n + (1ull << P.search_parts_log) - 1) >> P.search_parts_log);
+        cols = max((uint64_t)64, (per + 63) & ~63ull);
+        have = pc.m > 0 && (uint64_t)part * cols < (uint64_t)pc.n;
+    }
+    search_part(P, have, pair, pc, have ? (int)(part * cols) : 0, cols);
+}
+
+// Serving: the items of k_search_items (pair << 24 | chunk), one per lane.
+__global__ __launch_bounds__(64) void k_search_lane_items(AlignParams P) {
+    const uint32_t n_items = __hip_atomic_load(P.counters + kCounterListBase, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+    for (uint64_t first = (uint64_t)blockIdx.x * 64; first < n_items; first += (uint64_t)gridDim.x * 64) {
+        const uint64_t at = first + threadIdx.x;
+        bool have = at < n_items;
+        uint64_t pair = 0;
+        int c0 = 0;
+        PairCursor pc{0, 0, 0, 0, 0, 0};
+        if (have) {
+            const uint64_t it = P.items_in[at];
+            pair = it >> 24;
+            c0 = (int)((uint32_t)(it & 0xffffffull) * P.search_chunk);
+            pc = pair_cursor(P, pair);
+            have = c0 < pc.n;
+        }
+        search_part(P, have, pair, pc, c0, P.search_chunk);
+    }
 }
 
 // ---------------------------------------------------------------------------

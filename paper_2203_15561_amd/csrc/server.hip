@@ -213,7 +213,8 @@ struct genasm_server {
     genasm_server_config cfg{};
     AlignParams base{};   // fields common to every iteration's kernels
     int search_blocks = 0, win_blocks = 0;
-    uint32_t groups = 0;  // 16-lane window groups of the persistent grid
+    bool lanes = false;   // one pair per lane (windows that commit few enough bases)
+    uint32_t groups = 0;  // pairs in device slots that count as twice a busy device
     // s: the iterations; s_up: their uploads, which overlap the iteration
     // before; s_copy: completions to the host and the arrival count
     hipStream_t s = nullptr, s_up = nullptr, s_copy = nullptr;
@@ -231,7 +232,7 @@ struct genasm_server {
     uint32_t* d_new = nullptr;               // slots admitted in the running iteration
     uint32_t *d_fin = nullptr, *d_fin_len = nullptr;
     uint64_t* d_fin_off = nullptr;
-    uint64_t* d_items = nullptr;             // two start-search item lists
+    uint64_t* d_items = nullptr;             // start-search item lists (one with a pair per lane, else two)
     unsigned long long* d_key = nullptr;     // per-slot search key
     TurnLimits* d_turn = nullptr;            // the running iteration's turn limits
     unsigned long long* d_arrivals = nullptr;  // arrival count, copied from h_arrivals
@@ -310,16 +311,20 @@ hipError_t enqueue_iteration(genasm_server* srv, int q) {
     const uint64_t cap = srv->item_cap;
     S.list_slot = 0;
     S.items_in = srv->d_items;
-    S.items_out = srv->d_items + cap;
-    if ((e = launch_search(S, 16, 1, srv->search_blocks, s))) return e;
-    S.items_in = srv->d_items + cap;
-    S.items_out = srv->d_items;
-    S.list_slot = 1;
-    if ((e = launch_search(S, 16, 2, srv->search_blocks, s))) return e;
-    S.items_in = srv->d_items;
-    S.items_out = srv->d_items + cap;
-    S.list_slot = 2;
-    if ((e = launch_search(S, 16, 4, srv->search_blocks, s))) return e;
+    if (srv->lanes) {
+        if ((e = launch_search_lane_items(S, srv->search_blocks, s))) return e;
+    } else {
+        S.items_out = srv->d_items + cap;
+        if ((e = launch_search(S, 16, 1, srv->search_blocks, s))) return e;
+        S.items_in = srv->d_items + cap;
+        S.items_out = srv->d_items;
+        S.list_slot = 1;
+        if ((e = launch_search(S, 16, 2, srv->search_blocks, s))) return e;
+        S.items_in = srv->d_items;
+        S.items_out = srv->d_items + cap;
+        S.list_slot = 2;
+        if ((e = launch_search(S, 16, 4, srv->search_blocks, s))) return e;
+    }
     if ((e = launch_search_finalize(S, NS, s))) return e;
     // windows until the iteration's deadline
     if ((e = launch_serve_stamp(b.d_params, srv->d_turn, s))) return e;
@@ -332,7 +337,8 @@ hipError_t enqueue_iteration(genasm_server* srv, int q) {
     P.next_hot = nb.d_hot;
     P.next_cold = nb.d_cold;
     P.next_len = nb.d_cnt;
-    if ((e = launch_windows(P, srv->win_blocks, s))) return e;
+    if ((e = srv->lanes ? launch_windows_serve(P, srv->win_blocks, s) : launch_windows(P, srv->win_blocks, s)))
+        return e;
     return launch_serve_finish(srv->d_fin, srv->d_fin_len, srv->d_out, srv->d_fin_off, b.dh_hdr,
                                b.dh_slot, b.dh_res, srv->d_cigar, b.d_gather, srv->gather_cap, NS,
                                s);
@@ -377,8 +383,16 @@ int genasm_server_create(genasm_ctx* ctx, const genasm_server_config* cfg_in,
     const int per_cu = std::max(1, std::min(16, windows_blocks_per_cu(occ)));
     srv->win_blocks = ctx->num_cus * per_cu;
     srv->groups = (uint32_t)srv->win_blocks * 4;
+    srv->lanes = L <= kLanePathCommit;
+    if (srv->lanes) {
+        // a wavefront per SIMD (a workgroup has two), the pairs spread over all of
+        // them; the device counts as busy with 12 pairs in each
+        srv->win_blocks = ctx->num_cus * 2;
+        srv->groups = (uint32_t)srv->win_blocks * 24;
+    }
     srv->search_blocks = ctx->num_cus * 8;
-    const uint64_t workers = (uint64_t)srv->win_blocks * 4;
+    const uint64_t workers = srv->lanes ? 0 : (uint64_t)srv->win_blocks * 4;  // those that spill
+    const uint32_t search_chunk = srv->lanes ? kServeLaneSearchChunk : kServeSearchChunk;
     srv->upload_cap = 1ull << 24;
     srv->gather_cap = std::min<uint64_t>(cfg.pool_bases, 1ull << 23);
 
@@ -409,8 +423,8 @@ int genasm_server_create(genasm_ctx* ctx, const genasm_server_config* cfg_in,
     D(srv->d_read_len, NS); D(srv->d_ref_len, NS);
     D(srv->d_out, NS); D(srv->d_state, NS); D(srv->d_search, NS);
     D(srv->d_new, NS); D(srv->d_fin, NS); D(srv->d_fin_len, 4); D(srv->d_fin_off, NS);
-    srv->item_cap = search_item_cap(NS, cfg.pool_bases, kServeSearchChunk);
-    D(srv->d_items, 2 * srv->item_cap); D(srv->d_key, NS); D(srv->d_turn, 1);
+    srv->item_cap = search_item_cap(NS, cfg.pool_bases, search_chunk);
+    D(srv->d_items, (srv->lanes ? 1 : 2) * srv->item_cap); D(srv->d_key, NS); D(srv->d_turn, 1);
     D(srv->d_arrivals, 1); H(srv->h_arrivals, 1);
     D(srv->d_spill, spill_words(workers, kCompactSpillRows));
     for (IterBufs& b : srv->it) {
@@ -479,7 +493,7 @@ int genasm_server_create(genasm_ctx* ctx, const genasm_server_config* cfg_in,
     p.state = srv->d_state;
     p.window_budget = cfg.window_budget;
     p.search_key = srv->d_key;
-    p.search_chunk = kServeSearchChunk;
+    p.search_chunk = search_chunk;
     p.fin_list = srv->d_fin;
     p.fin_len = srv->d_fin_len;
 
