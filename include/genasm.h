@@ -88,13 +88,16 @@ typedef struct {
 #define GENASM_CIGAR_OP(e) ((e) & 3u)
 
 /* Launch forms. */
-#define GENASM_FORM_PLAIN 0    /* one pair per workgroup: 64 lanes = 64 DP rows of one pair */
-#define GENASM_FORM_BATCHED 1  /* search kernels, then a window kernel. With the default values
-                                  of every field below but workers_per_cu and lpt_order, and
-                                  W - O <= 40: one pair per lane, the window's rows kept as
-                                  differences along the read. With any other value: the row
-                                  tables of key ideas 1-3, several pairs per wavefront, a
-                                  persistent kernel with a device work queue */
+#define GENASM_FORM_PLAIN 0    /* one kernel, one pair per workgroup: a wavefront on the pair's
+                                  diagonals */
+#define GENASM_FORM_BATCHED 1  /* with the default values of every field below but
+                                  workers_per_cu and lpt_order: the plain form's kernel for a
+                                  batch of few pairs, else (when W - O <= 40) search and window
+                                  kernels that take one pair per lane, the window's rows kept
+                                  as differences along the read. With any other value: the row
+                                  tables of key ideas 1-3, several pairs per wavefront, search
+                                  kernels and a persistent window kernel with a device work
+                                  queue */
 #define GENASM_FORM_UNIMPROVED 2 /* ablation: one pair per workgroup, each window computing
                                   every row 0..K and keeping the four edge words of every
                                   entry in device memory (no early exit, no AND, no pruning);

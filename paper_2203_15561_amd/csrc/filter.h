@@ -51,15 +51,17 @@ struct FilterLane {
 
 // kFilterSteps columns, the rightmost first. text: bases of the block's columns;
 // out: bit t set where column t of the block lies outside the reference.
-// Returns the least (score << 6 | steps left), valid in a group's last lane.
-template <bool EDGE>
+// CHAIN: the rows below this lane's are the lane's before. Returns the least
+// (score << 6 | column of the block), valid in a group's last lane.
+template <bool EDGE, bool CHAIN>
 __device__ __forceinline__ uint32_t filter_block(FilterLane& f, u64 a, u64 b, u64 pad, uint32_t keep,
                                                  u64 text, uint32_t out) {
     const uint32_t tw[2] = {here((uint32_t)text), here((uint32_t)(text >> 32))};
     uint32_t best = ~0u;
 #pragma unroll
     for (int x = kFilterSteps - 1; x >= 0; --x) {
-        const uint32_t ph = from_lane_before(f.ph, keep), mh = from_lane_before(f.mh, keep);
+        const uint32_t ph = CHAIN ? from_lane_before(f.ph, keep) : 0u;
+        const uint32_t mh = CHAIN ? from_lane_before(f.mh, keep) : 0u;
         u64 ne = a ^ both(bit_mask(tw[x / 16], 2 * (x % 16)));
         uint32_t off = 0u;
         if constexpr (EDGE) {
@@ -138,8 +140,8 @@ __global__ __launch_bounds__(64) void k_filter(const uint8_t* reads, const uint6
         uint32_t out = 0u;
         if (top >= n) out |= n - c0 <= 0 ? ~0u : ~0u << (n - c0);
         if (c0 < 0) out |= c0 <= -kFilterSteps ? ~0u : ~(~0u << -c0);
-        const uint32_t k = __ballot(out != 0u) != 0ull ? filter_block<true>(f, a, b, pad, keep, text, out)
-                                                       : filter_block<false>(f, a, b, pad, keep, text, 0u);
+        const uint32_t k = __ballot(out != 0u) != 0ull ? filter_block<true, true>(f, a, b, pad, keep, text, out)
+                                                       : filter_block<false, true>(f, a, b, pad, keep, text, 0u);
         // a later block lies further left, so it wins ties
         if (k != ~0u && (int)(k >> 6) <= best) {
             best = (int)(k >> 6);

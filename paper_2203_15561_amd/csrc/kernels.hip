@@ -1194,37 +1194,6 @@ __device__ __forceinline__ void finish_without_windows(const AlignParams& P, uin
 }
 
 // ---------------------------------------------------------------------------
-// Plain form: one pair per workgroup, 64 lanes = 64 rows
-// ---------------------------------------------------------------------------
-
-__global__ __launch_bounds__(64) void k_plain(AlignParams P) {
-    extern __shared__ u64 smem[];
-    const int lane = threadIdx.x;
-    const uint64_t pair = blockIdx.x;
-    if (pair >= P.n_pairs) return;
-    const PairCursor pc = pair_cursor(P, pair);
-    if (pc.m == 0) {
-        if (lane == 0) finish_without_windows(P, pair, 0);
-        return;
-    }
-    const int m1 = min(P.W, pc.m);
-    const int Kr = min(P.K, m1 - 1);
-    build_pm<64>(smem, lane, P.reads, pc.rb, m1, false);
-    int row, col;
-    search_rows<64, 1>(smem, lane, lane, P.refs, pc.fb, pc.n, m1, Kr, &row, &col);
-    if (lane == 0)
-        search_stats(P, pair, pc.n, m1, row >= 0 ? row : (m1 <= P.K ? m1 : Kr), 64ull * (pc.n + 63), true);
-    if (row < 0) {
-        if (m1 <= P.K) { row = m1; col = 0; }   // row m1 hits in every column
-        else {
-            if (lane == 0) finish_without_windows(P, pair, -1);
-            return;
-        }
-    }
-    run_pair<64>(P, smem, nullptr, 64, lane, lane, pair, col);
-}
-
-// ---------------------------------------------------------------------------
 // Unimproved form (ablation): the GenASM window without the three improvements
 // ---------------------------------------------------------------------------
 //
@@ -2436,6 +2405,7 @@ __global__ void k_audit(AlignParams P, int queued) {
 
 #include "lanes.h"
 #include "filter.h"
+#include "wave_pair.h"
 
 // Copies each pair's CIGAR elements to dst + dst_off[pair] (one block per pair).
 __global__ void k_compact(const genasm_result* out, const uint64_t* dst_off, uint64_t n_pairs,
@@ -2465,8 +2435,9 @@ int search_lds_bytes(int group_lanes) { return (64 / group_lanes) * kSearchGroup
 
 hipError_t launch_plain(const AlignParams& p, hipStream_t s) {
     if (p.n_pairs == 0) return hipSuccess;
-    const int lds = plain_lds_bytes(p.stride);
-    hipLaunchKernelGGL(k_plain, dim3((unsigned)p.n_pairs), dim3(64), lds, s, p);
+    const dim3 grid((unsigned)p.n_pairs), block(64);
+    if (p.stats) hipLaunchKernelGGL(k_pair_wave<true>, grid, block, kWaveLdsBytes, s, p);
+    else hipLaunchKernelGGL(k_pair_wave<false>, grid, block, kWaveLdsBytes, s, p);
     return hipGetLastError();
 }
 

@@ -372,18 +372,32 @@ int genasm_pack_dev(genasm_ctx* ctx, const char* d_ascii, uint64_t n, uint8_t* d
 
 namespace {
 
-// Whether a batched launch takes the one-pair-per-lane path (lanes.h): the
-// default geometry of the row-table kernels, which any other value of these
-// fields asks for, and windows that commit no more bases than the path keeps
-// columns for. At 20,000 pairs of 10 kb the start search and the windows take
-// 0.25 and 1.8 ms on it, 2.7 and 15.6 ms on the row tables; it is also the
-// faster one for 1,000 reads of 100 bases (0.07 against 0.10 ms) and for 67
-// reads of 30 kb (4.2 against 13.7 ms).
-bool lane_path(const genasm_launch& L, int commit) {
+// Whether a batched launch leaves the kernels to the library: the default
+// geometry of the row-table kernels, which any other value of these fields asks
+// for.
+bool default_geometry(const genasm_launch& L) {
     return L.group_lanes == 16 && L.search_lanes == 16 && L.lds_rows == 16 && L.hard_row == 16 &&
            L.hard_lanes == 16 && L.tb_prefetch == 0 && L.hard_share == 50 && L.table_bits == 64 &&
-           L.search_per_cu == 8 && commit <= kLanePathCommit;
+           L.search_per_cu == 8;
 }
+
+// Whether such a launch takes one pair per wavefront, the plain form's kernel:
+// up to eight wavefronts per CU. Its windows cost a quarter to half of a lane's
+// (wave_pair.h) as long as the wavefronts have a SIMD to themselves and there is
+// one launch instead of seven: 4 reads of 150 bases take 20 us against 50, 1,000
+// of 100 24 against 47, 67 of 30 kb 1.5 ms against 3.9, 2,000 of 3 kb 451 us
+// against 489 (with 30% decoys 595 against 561), 8,000 of 3 kb 850 against 557.
+// Its start search has 64 parts whatever the reference, so much longer
+// references than reads go to the other path.
+bool wave_path(const genasm_ctx* ctx, uint64_t n_pairs, uint64_t total_ref_bases) {
+    return n_pairs <= (uint64_t)ctx->num_cus * 8 && total_ref_bases / n_pairs <= 65536;
+}
+
+// Whether it takes one pair per lane (lanes.h) otherwise: when its windows commit
+// no more bases than that path keeps columns for. At 20,000 pairs of 10 kb the
+// start search and the windows take 0.25 and 1.8 ms on it, 2.7 and 15.6 ms on the
+// row tables.
+bool lane_path(int commit) { return commit <= kLanePathCommit; }
 
 // The batched form on that path: planes and cleared search keys, the order,
 // the start search, the windows. Scratch comes from `carved` (enough for the
@@ -569,17 +583,16 @@ int align_dev(genasm_ctx* ctx, const uint8_t* d_reads2b, const uint64_t* d_read_
         CHECK_HIP(ctx, mark(3));
         return GENASM_OK;
     }
-    if (L.form == GENASM_FORM_PLAIN) {
-        p.lds_rows = 64;
+    auto plain = [&]() -> int {
         CHECK_HIP(ctx, mark(0));
-        CHECK_HIP(ctx, planes());
         CHECK_HIP(ctx, mark(1));
         CHECK_HIP(ctx, mark(2));
         CHECK_HIP(ctx, launch_plain(p, s));
         CHECK_HIP(ctx, launch_audit(p, 0, s));  // debug builds only
         CHECK_HIP(ctx, mark(3));
         return GENASM_OK;
-    }
+    };
+    if (L.form == GENASM_FORM_PLAIN) return plain();
 
     // Batched: scratch layout.
     p.lds_rows = L.lds_rows;
@@ -594,7 +607,8 @@ int align_dev(genasm_ctx* ctx, const uint8_t* d_reads2b, const uint64_t* d_read_
     // more resident search workgroups than 8 per CU make smaller chunks (each
     // rescanning m1 + 64 columns past its end) and measured slower
     const int search_blocks = ctx->num_cus * L.search_per_cu;
-    const bool lanes = lane_path(L, p.L);
+    const bool waves = default_geometry(L) && wave_path(ctx, n_pairs, total_ref_bases);
+    const bool lanes = default_geometry(L) && !waves && lane_path(p.L);
     const int spill_rows = p.compact ? kCompactSpillRows : 64 - L.lds_rows;
     // Search chunks: at least kBatchSearchChunk columns, and large enough that
     // the batch makes about two items per search group (counted at 8 search
@@ -629,6 +643,8 @@ int align_dev(genasm_ctx* ctx, const uint8_t* d_reads2b, const uint64_t* d_read_
         return dry.off + 256;
     };
     int per_cu = L.workers_per_cu;
+    // (the no-allocation call still refuses what the row-table layout would)
+    if (waves && !noalloc) return plain();
     if (lanes && !noalloc) {
         // no spill, no item lists; the no-allocation call keeps the layout below, so
         // that it takes the same batches as ever
@@ -657,6 +673,7 @@ int align_dev(genasm_ctx* ctx, const uint8_t* d_reads2b, const uint64_t* d_read_
     if (profiling) ctx->prof_window_blocks = win_blocks;
     Carver real{base};
     real.off = base_off;
+    if (waves) return plain();
     if (lanes) return align_lanes(ctx, p, L, total_read_bases, total_ref_bases, &real, mark, s);
     auto [items, hist, order] = carve(real, workers);
 

@@ -1,0 +1,465 @@
+// One pair per wavefront: start search and windows in one kernel, for the plain
+// form and for batches too small to fill the chip a pair per lane.
+//
+// A window on diagonals. E(i, j) is the distance of diff_window.h. Along a
+// diagonal (j - i fixed) it never grows towards the end, so the cells with E <=
+// d are those from a first text base f_d on; level d is one number per
+// diagonal, and with a diagonal per lane a level is one step for all of them:
+//   f_d(t) = the least i from which the bases of diagonal t match up to
+//            min(f_d-1(t) - 1, f_d-1(t + 1), f_d-1(t - 1) - 1)
+// (a substitution, an insertion or a deletion before a cell of the level
+// below), and level 0 starts from the read window's end. (Ukkonen, Algorithms
+// for approximate string matching, 1985, from the end and with a free text
+// end.) d* is the first level that reaches (0, 0). The traceback asks for E of
+// neighbouring cells against d - 1 only, which is f_d-1 of their diagonals. A
+// level costs about 20 instructions, so a window costs by its distance: about
+// 2 us at d* = 6 and 5 us at d* = 33, where a lane's column-by-column step
+// (diff_window.h) takes 5 us, for up to 64 pairs at once.
+//
+// An alignment of d edits from (0, 0) stays on diagonals -(d + nw - mw) / 2 .. d:
+// past -x it needs x deletions, and then x + mw - nw insertions to reach the
+// read window's end. So 64 diagonals from -kBandBelow on give the exact answer
+// up to d = 42 (two full windows), and the rare rest is done again with all 128.
+#pragma once
+
+#include "diff_window.h"
+
+constexpr int kBandBelow = 21;
+constexpr int kNoCell = 0x4000;    // f of a diagonal without a cell at that level, or near it
+// A diagonal's levels 0..64 (and up to 3 computed past them), one byte each, side by side: only its
+// lane writes and reads them, four at a time on the way back (17 words apart,
+// so the lanes' words lie in different banks).
+constexpr int kWaveLevels = 68;
+constexpr int kWaveLdsBytes = kWaveLevels * 128;
+
+// Cross-lane moves over the whole wavefront. Values the others call with are
+// the same in every lane (lane numbers, and what readlane returns).
+__device__ __forceinline__ int read_lane(int v, int lane) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_readlane(v, lane);
+#else
+    return __shfl(v, lane);
+#endif
+}
+// The next (previous) lane's value; the last (first) lane gets `edge`.
+__device__ __forceinline__ int lane_above(int v, int edge, int lane) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    (void)lane;
+    return __builtin_amdgcn_update_dpp(edge, v, 0x130 /* wave_shl:1 */, 0xF, 0xF, false);
+#else
+    const int x = __shfl(v, (lane + 1) & 63);
+    return lane == 63 ? edge : x;
+#endif
+}
+__device__ __forceinline__ int lane_below(int v, int edge, int lane) {
+    (void)lane;
+    return __builtin_amdgcn_update_dpp(edge, v, kDppWaveShr1, 0xF, 0xF, false);
+}
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ u64 uniform64(u64 v) {
+    return ((u64)(uint32_t)uniform((int)(v >> 32)) << 32) | (uint32_t)uniform((int)v);
+}
+__device__ __forceinline__ u64 wave_min(u64 v, int lane) {
+    for (int s = 1; s < 64; s <<= 1) v = min(v, (u64)__shfl(v, lane ^ s));
+    return uniform64(v);
+}
+
+// A sequence read forward in blocks of 64 bases: two blocks as bit planes, the
+// same in every lane, and the codes of the block after them on their way, one
+// base per lane.
+struct WaveSeq {
+    const uint8_t* s;
+    uint64_t base;  // stream offset of the sequence
+    int len, block;
+    u64 lo0, lo1, hi0, hi1;
+    int next;  // the byte that holds the lane's code, shifted only when it is used
+};
+__device__ __forceinline__ int wave_seq_byte(const WaveSeq& q, int block, int lane) {
+    const int64_t at = (int64_t)block * 64 + lane;
+    return at < (int64_t)q.len ? (int)q.s[(q.base + (uint64_t)at) >> 2] : 0;
+}
+__device__ __forceinline__ int wave_seq_code(const WaveSeq& q, int byte, int lane) {
+    return byte >> (2 * (int)((q.base + (uint64_t)lane) & 3u));  // blocks are whole bytes long
+}
+__device__ __forceinline__ void wave_seq_open(WaveSeq& q, const uint8_t* s, uint64_t base, int len, int at,
+                                              int lane) {
+    q.s = s;
+    q.base = base;
+    q.len = len;
+    q.block = at >> 6;
+    const int b0 = wave_seq_byte(q, q.block, lane), b1 = wave_seq_byte(q, q.block + 1, lane);
+    q.next = wave_seq_byte(q, q.block + 2, lane);
+    const int c0 = wave_seq_code(q, b0, lane), c1 = wave_seq_code(q, b1, lane);
+    q.lo0 = __ballot(c0 & 1);
+    q.hi0 = __ballot(c0 & 2);
+    q.lo1 = __ballot(c1 & 1);
+    q.hi1 = __ballot(c1 & 2);
+}
+// The 64 bases from `at` on (at most a block further than the last call's).
+__device__ __forceinline__ void wave_seq_window(WaveSeq& q, int at, int lane, u64& lo, u64& hi) {
+    if ((at >> 6) != q.block) {
+        q.lo0 = q.lo1;
+        q.hi0 = q.hi1;
+        const int c = wave_seq_code(q, q.next, lane);
+        q.lo1 = __ballot(c & 1);
+        q.hi1 = __ballot(c & 2);
+        ++q.block;
+        q.next = wave_seq_byte(q, q.block + 2, lane);
+    }
+    lo = funnel64(q.lo0, q.lo1, at & 63);
+    hi = funnel64(q.hi0, q.hi1, at & 63);
+}
+
+// The diagonals of a window: lane l of set s holds diagonal 64 s + l - below.
+template <int SETS> struct WaveWindow {
+    static constexpr int below = SETS == 1 ? kBandBelow : 63;  // two sets: -63 .. 64
+    u64 ne[SETS];  // bit i: text base i and the diagonal's read base differ, or there is no such cell
+};
+
+template <int SETS>
+__device__ __forceinline__ void wave_window(WaveWindow<SETS>& w, u64 pl, u64 ph, u64 tl, u64 th, int lane) {
+#pragma unroll
+    for (int s = 0; s < SETS; ++s) {
+        const int t = 64 * s + lane - WaveWindow<SETS>::below;
+        const int r = max(t, 0) & 63, l = max(-t, 0);
+        const u64 m = l >= 64 ? ~0ull : ~(~0ull << l);  // cells before the read window's start
+        const u64 a = (pl >> r) << (l & 63), b = (ph >> r) << (l & 63);
+        w.ne[s] = (a ^ tl) | (b ^ th) | m;
+    }
+}
+
+// Levels 0.. into lev; returns the first that reaches (0, 0), or -1 when none up
+// to d_max does.
+template <int SETS>
+__device__ __forceinline__ int wave_levels(const WaveWindow<SETS>& w, uint8_t* lev, int mw, int nw, int d_max,
+                                           int lane) {
+    constexpr int below = WaveWindow<SETS>::below;
+    // f negated, so that it is the extension's shift count (modulo 64) as it is
+    int g[SETS], first[SETS];
+#pragma unroll
+    for (int s = 0; s < SETS; ++s) {
+        const int t = 64 * s + lane - below;
+        first[s] = min(t, 0);
+        // the read window's end, where the diagonal reaches it inside the text
+        g[s] = mw - t >= -first[s] && mw - t <= nw ? t - mw : -kNoCell;
+    }
+    uint8_t* out[SETS];
+#pragma unroll
+    for (int s = 0; s < SETS; ++s) out[s] = lev + (64 * s + lane) * kWaveLevels;
+    // matches before text base f, then the level's byte (of a diagonal without a
+    // cell a number that stays far above 64 over 65 levels); whether it reaches
+    // (0, 0)
+    auto extend = [&](int d) -> bool {
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) {
+            const u64 x = w.ne[s] << (g[s] & 63);
+            const uint32_t run = min((uint32_t)(x ? __builtin_clzll(x) : 64), (uint32_t)-g[s]);
+            g[s] += (int)run;
+            out[s][d] = (uint8_t)min((uint32_t)-g[s], 255u);
+        }
+        return read_lane(g[below / 64], below & 63) == 0;
+    };
+    auto level = [&](int d) -> bool {  // d > 0: from the level before
+        int up[SETS], dn[SETS];
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) {
+            up[s] = lane_above(g[s], s + 1 < SETS ? read_lane(g[s + 1 < SETS ? s + 1 : s], 0) : -kNoCell, lane);
+            dn[s] = lane_below(g[s], s > 0 ? read_lane(g[s > 0 ? s - 1 : s], 63) : -kNoCell, lane);
+        }
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) g[s] = min(max(max(g[s], dn[s]) + 1, up[s]), first[s]);
+        return extend(d);
+    };
+    if (extend(0)) return 0;
+    int d = 1;
+    for (; d <= d_max; d += 4) {
+        if (level(d)) break;
+        if (level(d + 1)) { d += 1; break; }
+        if (level(d + 2)) { d += 2; break; }
+        if (level(d + 3)) { d += 3; break; }
+    }
+    return d <= d_max ? d : -1;
+}
+
+// The runs of a pair's CIGAR, the same in every lane.
+struct WaveRuns {
+    int cur_op;
+    uint32_t cur_len, written, room;
+    uint32_t* at;
+};
+__device__ __forceinline__ void wave_put(const WaveRuns& r, uint32_t index, uint32_t len, int op) {
+    if (index < r.room) r.at[index] = (len << 2) | (uint32_t)op;
+}
+__device__ __forceinline__ void wave_run(WaveRuns& r, int op, int len, int lane) {
+    if (op != r.cur_op) {
+        if (r.cur_op >= 0) {
+            if (lane == 0) wave_put(r, r.written, r.cur_len, r.cur_op);
+            ++r.written;
+        }
+        r.cur_op = op;
+        r.cur_len = 0u;
+    }
+    r.cur_len += (uint32_t)len;
+}
+
+// Appends a window's edits, one per lane (lane e < n: the matches before the
+// edit and its op), all at once: an edit starts a run unless it follows one of
+// the same op without a match between; a run's place is the number of runs
+// before it and its length the distance to the next start.
+__device__ __forceinline__ void wave_edits(WaveRuns& r, int n, int matches, int op, int lane) {
+    const bool have = lane < n;
+    const int before = lane_below(op, -1, lane);
+    const bool m = have && matches > 0, start = have && (matches > 0 || op != before);
+    const u64 M = __ballot(m), S = __ballot(start);
+    const u64 below = (1ull << lane) - 1ull;
+    const int first_op = (M & 1ull) ? (int)GENASM_OP_MATCH : read_lane(op, 0);
+    uint32_t open = 0u;  // length the first run takes over from the open one
+    if (r.cur_op == first_op) {
+        open = r.cur_len;
+    } else if (r.cur_op >= 0) {
+        if (lane == 0) wave_put(r, r.written, r.cur_len, r.cur_op);
+        ++r.written;
+    }
+    const int last = 63 - __builtin_clzll(S);  // the last run stays open
+    const u64 later = lane < 63 ? S >> (lane + 1) : 0ull;
+    const int len = later ? 1 + __builtin_ctzll(later) : n - lane;
+    const uint32_t at = r.written + (uint32_t)(__builtin_popcountll(M & below) + __builtin_popcountll(S & below));
+    if (m) wave_put(r, at, (uint32_t)matches + (lane == 0 ? open : 0u), (int)GENASM_OP_MATCH);
+    if (start && lane != last)
+        wave_put(r, at + (m ? 1u : 0u), (uint32_t)len + (lane == 0 && !m ? open : 0u), op);
+    r.written += (uint32_t)(__builtin_popcountll(M) + __builtin_popcountll(S)) - 1u;
+    r.cur_op = read_lane(op, last);
+    r.cur_len = (uint32_t)(n - last) + (last == 0 && !(M & 1ull) ? open : 0u);
+}
+
+// Traceback of a window of distance d from (0, 0); returns the edits it
+// commits. Each edit lowers d by one, so the levels are read in order, four to a
+// word and a word ahead of its use.
+template <int SETS>
+__device__ __forceinline__ int wave_trace(const WaveWindow<SETS>& w, const uint8_t* lev, int mw, int nw, int d,
+                                          int L, int lane, WaveRuns& runs, int& i_end, int& j_end) {
+    constexpr int below = WaveWindow<SETS>::below;
+    const int j_max = min(mw, L), i_max = min(L, nw);
+    auto load = [&](int level, int s) -> int {
+        return *reinterpret_cast<const int*>(lev + (64 * s + lane) * kWaveLevels + (max(level, 0) & ~3));
+    };
+    int i = 0, x = below;  // text base and diagonal index: read base j = i + x - below
+    int n = 0, tail = 0;
+    int edit = -1;         // lane e: edit e's matches before it << 2 | op
+    int level = d - 1;     // the one the next edit asks
+    int f[SETS], next[SETS];
+#pragma unroll
+    for (int s = 0; s < SETS; ++s) {
+        f[s] = load(level, s);
+        next[s] = load(level - 4, s);
+    }
+    for (;;) {
+        const int limit = min(i_max, j_max + below - x);  // the diagonal's last committed text base + 1
+        u64 ne = 0;
+#pragma unroll
+        for (int s = 0; s < SETS; ++s)
+            if (SETS == 1 || (x >> 6) == s)
+                ne = ((u64)(uint32_t)read_lane((int)(w.ne[s] >> 32), x & 63) << 32) |
+                     (uint32_t)read_lane((int)w.ne[s], x & 63);
+        const int k = min(ctz64(ne >> (i & 63)), limit - i);
+        i += k;
+        if (i >= limit || level < 0) {
+            tail = k;
+            break;
+        }
+        int fs = 0, fi = 0;  // that level on this diagonal and the next
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) {
+            if (SETS == 1 || (x >> 6) == s) fs = read_lane(f[s], x & 63);
+            if (SETS == 1 || ((x + 1) >> 6) == s) fi = read_lane(f[s], (x + 1) & 63);
+        }
+        const int at = 8 * (level & 3);
+        fs = (int)((uint32_t)fs >> at) & 255;
+        fi = (int)((uint32_t)fi >> at) & 255;
+        // the op, and what it adds to the text base (bit 2) and to the diagonal (from bit 3)
+        int e = fi <= i ? (int)GENASM_OP_INS | 8 : (int)GENASM_OP_DEL | 4 | -8;
+        e = fs <= i + 1 ? (int)GENASM_OP_MISMATCH | 4 : e;
+        if (lane == n) edit = (k << 2) | (e & 3);
+        ++n;
+        i += (e >> 2) & 1;
+        x += e >> 3;
+        if (at == 0) {
+#pragma unroll
+            for (int s = 0; s < SETS; ++s) {
+                f[s] = next[s];
+                next[s] = load(level - 5, s);
+            }
+        }
+        --level;
+    }
+    const int j = i + x - below;
+    if (n > 0) wave_edits(runs, n, edit >> 2, edit & 3, lane);
+    if (tail > 0) wave_run(runs, (int)GENASM_OP_MATCH, tail, lane);
+    // past the text only insertions are left
+    const int rest = i < L && j < j_max ? j_max - j : 0;
+    if (rest > 0) wave_run(runs, (int)GENASM_OP_INS, rest, lane);
+    i_end = i;
+    j_end = j + rest;
+    return n + rest;
+}
+
+// A window: distance (-1: above K) and, when it is solved, its traceback.
+template <int SETS>
+__device__ __forceinline__ int wave_solve(u64 pl, u64 ph, u64 tl, u64 th, int mw, int nw, int K, int L,
+                                          uint8_t* lev, int lane, WaveRuns& runs, int& edits, int& i_end,
+                                          int& j_end, bool& exact) {
+    WaveWindow<SETS> w;
+    wave_window<SETS>(w, pl, ph, tl, th, lane);
+    const int d_max = SETS == 1 ? min(K, 63 - kBandBelow) : K;
+    const int d = wave_levels<SETS>(w, lev, mw, nw, d_max, lane);
+    exact = SETS == 2;
+    if (SETS == 1) {
+        // no answer within K edits is one too when the band holds all of them
+        const int e = d >= 0 ? d : d_max;
+        exact = min(e, (e + nw - mw) / 2) <= kBandBelow && (d >= 0 || K <= 63 - kBandBelow);
+    }
+    if (!exact || d < 0) return -1;
+    edits = wave_trace<SETS>(w, lev, mw, nw, d, L, lane, runs, i_end, j_end);
+    return d;
+}
+
+// Start search: the wavefront's lanes take parts of the reference; see
+// search_part. A hit within Kr rows reaches at most m1 + Kr columns.
+__device__ __forceinline__ u64 wave_search(const AlignParams& P, const PairCursor& pc, int m1, int Kr, u64 pl,
+                                           u64 ph, int lane) {
+    const uint64_t bytes = (P.ref_off[P.n_pairs] + 3) / 4;
+    const int cols = max((pc.n + 63) / 64, 1);
+    const int64_t c0 = (int64_t)lane * cols;
+    const int e = (int)min((int64_t)pc.n, c0 + cols + m1 + Kr);
+    int nb = c0 < pc.n ? (int)((e - c0 + 31) / 32) : 0;
+    const u64 a = __builtin_bitreverse64(pl), b = __builtin_bitreverse64(ph);
+    const u64 pad = m1 < 64 ? (1ull << (64 - m1)) - 1 : 0ull;
+    FilterLane f{{~pad, 0ull}, 0u, 0u, m1};
+    u64 key = ~0ull;
+    u64 next = nb > 0 ? packed_bases(P.refs, bytes, (int64_t)pc.fb + c0 + 32 * (nb - 1)) : 0ull;
+    while (__ballot(nb > 0) != 0ull) {
+        const int64_t col = c0 + 32 * (int64_t)(nb - 1);
+        const u64 text = next;
+        if (nb > 1) next = packed_bases(P.refs, bytes, (int64_t)pc.fb + col - 32);
+        const int64_t valid = e - col;
+        const uint32_t out = nb > 0 && valid >= 32 ? 0u : nb > 0 ? ~0u << (int)valid : ~0u;
+        const uint32_t k = __ballot(out != 0u) != 0ull ? filter_block<true, false>(f, a, b, pad, 0u, text, out)
+                                                       : filter_block<false, false>(f, a, b, pad, 0u, text, 0u);
+        if (k != ~0u) key = min(key, ((u64)(k >> 6) << 32) | (u64)(uint32_t)(col + (int64_t)(k & 63u)));
+        --nb;
+    }
+    key = wave_min(key, lane);
+    return (int)(key >> 32) <= Kr ? key : ~0ull;
+}
+
+template <bool STATS>
+__global__ __launch_bounds__(64) void k_pair_wave(AlignParams P) {
+    extern __shared__ u64 smem[];
+    const int lane = threadIdx.x & 63;
+    const uint64_t pair = blockIdx.x;
+    if (pair >= P.n_pairs) return;
+    PairCursor pc = pair_cursor(P, pair);
+    pc.rb = uniform64(pc.rb);
+    pc.fb = uniform64(pc.fb);
+    pc.m = uniform(pc.m);
+    pc.n = uniform(pc.n);
+    if (pc.m == 0) {
+        if (lane == 0) finish_without_windows(P, pair, 0);
+        return;
+    }
+    uint8_t* lev = reinterpret_cast<uint8_t*>(smem);
+    WaveSeq rd, rf;
+    u64 pl, ph, tl, th;
+    wave_seq_open(rd, P.reads, pc.rb, pc.m, 0, lane);
+    wave_seq_window(rd, 0, lane, pl, ph);
+    const int m1 = min(P.W, pc.m);
+    const int Kr = min(P.K, m1 - 1);
+    const u64 key = wave_search(P, pc, m1, Kr, pl, ph, lane);
+    int row = -1, col = 0;
+    if (key != ~0ull) {
+        row = (int)(key >> 32);
+        col = (int)(uint32_t)key;
+    } else if (m1 <= P.K) {
+        row = m1;  // row m1 hits in every column
+    }
+    if (STATS && lane == 0) search_stats(P, pair, pc.n, m1, row >= 0 ? row : Kr, (u64)pc.n, true);
+    if (row < 0) {
+        if (lane == 0) finish_without_windows(P, pair, -1);
+        return;
+    }
+    const uint64_t base = uniform64(pair_run_base(P, pair));
+    const uint64_t limit = min(P.cigar_cap, base + (uint64_t)pc.m + (uint64_t)pc.n);
+    WaveRuns runs{-1, 0u, 0u, (uint32_t)uniform((int)(limit > base ? limit - base : 0ull)), P.cigar + base};
+    wave_seq_open(rf, P.refs, pc.fb, pc.n, col, lane);
+    int ti = col, pj = 0, score = 0;
+    uint32_t nwin = 0;
+    bool failed = false, internal = false;
+    u64 st_wops = 0, st_cells = 0, st_table = 0, st_tb = 0, st_steps = 0;
+    // every window commits at least one base, so a pair has at most m + n
+    const uint32_t max_windows = (uint32_t)pc.m + (uint32_t)pc.n;
+    while (pj < pc.m) {
+        if (nwin >= max_windows) {
+            failed = internal = true;
+            break;
+        }
+        const int mw = min(P.W, pc.m - pj), nw = min(P.W, pc.n - ti);
+        if (!audit_ok(P, pair, kAuditWindow, P.W >= 2 && P.W <= 64 && mw >= 1 && nw >= 0)) {
+            failed = internal = true;
+            break;
+        }
+        ++nwin;
+        wave_seq_window(rd, pj, lane, pl, ph);
+        wave_seq_window(rf, ti, lane, tl, th);
+        int edits = 0, i_end = 0, j_end = 0, d;
+        if (nw == 0) {  // past the text: insertions only
+            d = mw <= P.K ? mw : -1;
+            edits = j_end = min(mw, P.L);
+            if (d >= 0) wave_run(runs, (int)GENASM_OP_INS, edits, lane);
+        } else {
+            bool exact = false;
+            d = wave_solve<1>(pl, ph, tl, th, mw, nw, P.K, P.L, lev, lane, runs, edits, i_end, j_end, exact);
+            if (!exact)
+                d = wave_solve<2>(pl, ph, tl, th, mw, nw, P.K, P.L, lev, lane, runs, edits, i_end, j_end, exact);
+        }
+        if constexpr (STATS) {
+            st_cells += (u64)mw * nw;
+            st_steps += (u64)nw;
+        }
+        if (d < 0) {
+            failed = true;
+            break;
+        }
+        if constexpr (STATS) {
+            st_wops += (u64)nw * (2 + 6 * (u64)d);
+            st_table += (u64)(d + 1) * (min(nw, P.L) + 1);
+            st_tb += 2 * (u64)edits;
+        }
+        score += edits;
+        ti += i_end;
+        pj += j_end;
+    }
+    if (lane != 0) return;
+    if (!failed && runs.cur_op >= 0) {
+        wave_put(runs, runs.written, runs.cur_len, runs.cur_op);
+        ++runs.written;
+    }
+    const bool overflow = runs.written > runs.room;
+    genasm_result r;
+    r.edit_distance = failed ? -1 : score;
+    r.ref_begin = failed ? 0u : (uint32_t)col;
+    r.ref_end = failed ? 0u : (uint32_t)ti;
+    r.cigar_len = failed || overflow ? 0u : runs.written;
+    r.n_windows = nwin;
+    r.cigar_off = base;
+    r.flags = (overflow && !failed ? GENASM_FLAG_CIGAR_OVERFLOW : 0u) | (internal ? GENASM_FLAG_INTERNAL : 0u);
+    P.out[pair] = r;
+    if constexpr (STATS) {
+        u64* stp = P.stats + pair * kStatCount;
+        stp[kStatWindowWordOps] += st_wops;
+        stp[kStatWindowCells] += st_cells;
+        stp[kStatTableWords] += st_table;
+        stp[kStatTbReads] += st_tb;
+        stp[kStatWindowLaneSteps] += st_steps;
+        stp[kStatWindows] += nwin;
+    }
+}

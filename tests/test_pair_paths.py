@@ -1,7 +1,9 @@
-"""The one-pair-per-lane path (csrc/lanes.h): its window on the CPU against a
-textbook dynamic program, and the batched launch that takes it against the
-oracle at the sizes where its launch, its blocks of columns and its short
-windows have their edges."""
+"""The paths that take one pair per lane (csrc/lanes.h) and one pair per
+wavefront (csrc/wave_pair.h): a lane's window on the CPU against a textbook
+dynamic program, the wavefront's kernel under the CPU emulation and both paths
+on the GPU against the oracle at the sizes where their launches, their blocks
+of columns, their bands of diagonals and their short windows have their
+edges; and the filter at its edges."""
 import os
 import subprocess
 
@@ -11,6 +13,7 @@ import pytest
 import oracle
 import paper_2203_15561_amd as ga
 from tests._helpers import rle
+from tests.emu import run as emu
 from workloads import gen
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -42,29 +45,49 @@ def pairs_of(n, seed, read_len, ref_len):
     return reads, refs
 
 
+def expected_of(ps):
+    res, ops, _, _ = oracle.batch(ps)
+    return [(int(res["score"][i]), rle(oracle.pair_ops(ps, res, ops, i)) if res["score"][i] >= 0 else "",
+             int(res["ref_begin"][i]) if res["score"][i] >= 0 else 0,
+             int(res["ref_end"][i]) if res["score"][i] >= 0 else 0, int(res["n_windows"][i]))
+            for i in range(ps.n_pairs)]
+
+
+@pytest.mark.slow
+def test_wavefront_kernel_emulated(tmp_path):
+    # every overlap and cap, unrelated pairs (distances past the band of 64
+    # diagonals, which take the full band), reads past their reference's end
+    driver = emu.build(str(tmp_path / "emu_driver"))
+    reads, refs = pairs_of(9, 31, [70, 1, 64, 103], [90, 0, 64, 20])
+    for W, O, k in ((64, 24, 64), (64, 0, 64), (64, 63, 20), (33, 9, 7), (2, 1, 1)):
+        ps = gen.from_lists("wave", reads, refs, k, W, O)
+        res, cig = emu.run(driver, ps, 0, 16, 16, 16)
+        got = [(int(r["edit_distance"]), c, int(r["ref_begin"]), int(r["ref_end"]), int(r["n_windows"]))
+               for r, c in zip(res, cig)]
+        assert (res["flags"] == 0).all() and got == expected_of(ps), (W, O, k)
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("n", [1, 2, 63, 65, 513, 1025])
+@pytest.mark.parametrize("n,form", [(1, None), (65, None), (2047, None), (2048, ga.FORM_PLAIN),
+                                    (2049, None), (4097, None), (33_001, None)])
 @pytest.mark.parametrize("W,O,k", [(64, 24, 64), (64, 24, 9), (64, 32, 64), (64, 23, 64), (33, 9, 64),
                                    (40, 0, 40), (8, 7, 3)])
-def test_batched_launch_at_its_edges(n, W, O, k):
-    # 1 to 64 pairs per wavefront and a last wavefront that is not full; reads
-    # and references around 0, 1, 40, 64 and 128 bases and around several search
-    # parts; W - O of 40 and less (the lane path) and of 41 (the row tables)
+def test_batched_launch_at_its_edges(n, form, W, O, k):
+    # up to 2,048 pairs one per wavefront, past that 8, 16 and 64 pairs per
+    # wavefront and a last one that is not full; reads and references around 0, 1,
+    # 40, 64 and 128 bases and around several search parts, unrelated pairs (deep
+    # windows); W - O of 40 and less (the lane path) and of 41 (the row tables)
     reads, refs = pairs_of(n, 900 + W + O, [150, 0, 1, 39, 40, 41, 63, 64, 65, 104, 129, 600],
                            [170, 64, 0, 1, 63, 65, 128, 129, 640, 1500])
     ps = gen.from_lists("edges", reads, refs, k, W, O)
-    res_o, ops_o, _, _ = oracle.batch(ps)
+    want_all = expected_of(ps)
     with ga.Context(0) as ctx:
-        res, cig = ctx.align(reads, refs, k, W, O)
+        res, cig = ctx.align(reads, refs, k, W, O, None if form is None else ga.make_launch(form))
     assert (res["flags"] == 0).all()
     for i in range(n):
-        sc = int(res_o["score"][i])
-        want = (sc, rle(oracle.pair_ops(ps, res_o, ops_o, i)) if sc >= 0 else "",
-                int(res_o["ref_begin"][i]) if sc >= 0 else 0, int(res_o["ref_end"][i]) if sc >= 0 else 0,
-                int(res_o["n_windows"][i]))
         r = res[i]
         got = (int(r["edit_distance"]), cig[i], int(r["ref_begin"]), int(r["ref_end"]), int(r["n_windows"]))
-        assert got == want, (i, len(reads[i]), len(refs[i]), got, want)
+        assert got == want_all[i], (i, len(reads[i]), len(refs[i]), got, want_all[i])
 
 
 @pytest.mark.gpu
