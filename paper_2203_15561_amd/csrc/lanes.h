@@ -3,6 +3,8 @@
 #pragma once
 
 #include "diff_window.h"
+#include "filter.h"
+#include "wave_pair.h"
 
 static_assert(kLaneCols == kLanePathCommit, "the launch rule and the kernels agree");
 
@@ -96,8 +98,8 @@ __device__ __forceinline__ void mail_barrier() {
 #endif
 }
 
-// A lane's pairs: lane l of workgroup b takes list position b * lanes + l, then
-// every gridDim * lanes further on. Serving: the resident pairs, those that
+// A lane's pairs: lane l of the b-th workgroup of lanes takes list position
+// b * lanes + l, then every (their number) * lanes further on. Serving: the resident pairs, those that
 // advanced least first; otherwise all pairs, longest reads first if ordered.
 struct LaneShare {
     uint64_t n, stride, first;
@@ -117,6 +119,9 @@ __device__ __forceinline__ LaneShare lane_share(const AlignParams& P) {
     } else {
         s.n = P.n_pairs;
         s.lanes = P.pair_lanes;
+        s.stride = (uint64_t)((int)gridDim.x - P.long_blocks) * s.lanes;
+        s.first = (uint64_t)P.long_pairs + (uint64_t)((int)blockIdx.x - P.long_blocks) * s.lanes;
+        return s;
     }
     s.stride = (uint64_t)gridDim.x * s.lanes;
     s.first = (uint64_t)blockIdx.x * s.lanes;
@@ -125,8 +130,8 @@ __device__ __forceinline__ LaneShare lane_share(const AlignParams& P) {
 
 // The wavefront that computes the windows.
 template <bool STATS, bool SERVE>
-__device__ __forceinline__ void windows_compute(const AlignParams& P, LaneMail& mail, int lane) {
-    const LaneShare share = lane_share<SERVE>(P);
+__device__ __forceinline__ void windows_compute(const AlignParams& P, const LaneShare& share, LaneMail& mail,
+                                                int lane) {
     const uint64_t rorg = P.planes_from_off0 ? (P.read_off[0] & ~63ull) : 0;
     const uint64_t forg = P.planes_from_off0 ? (P.ref_off[0] & ~63ull) : 0;
     TurnClock turn;
@@ -267,8 +272,8 @@ __device__ __forceinline__ void windows_compute(const AlignParams& P, LaneMail& 
 
 // The wavefront that writes the CIGARs and results, a window behind the other.
 template <bool STATS, bool SERVE>
-__device__ __forceinline__ void windows_write(const AlignParams& P, const LaneMail& mail, int lane) {
-    const LaneShare share = lane_share<SERVE>(P);
+__device__ __forceinline__ void windows_write(const AlignParams& P, const LaneShare& share, const LaneMail& mail,
+                                              int lane) {
     int buf = 0;
     for (uint64_t first = share.first; first < share.n; first += share.stride) {
         bool more = true, opened = false;
@@ -370,12 +375,31 @@ __device__ __forceinline__ void windows_write(const AlignParams& P, const LaneMa
 // Window kernel, two wavefronts per workgroup and one pair per lane of them:
 // one computes the windows, the other turns each window's path into CIGAR runs
 // while the next window is computed.
+//
+// A lane's window takes 5 us and a batch as long as its longest pair. The first
+// P.long_blocks workgroups therefore take the P.long_pairs longest pairs a
+// wavefront each (wave_pair.h: 2 us a window); so do all workgroups of a serving
+// iteration with no more resident pairs than wavefronts.
 template <bool STATS, bool SERVE>
 __global__ __launch_bounds__(128, 2) void k_windows_lane(AlignParams P) {
-    __shared__ LaneMail mail;
-    const int lane = threadIdx.x & 63;
-    if (threadIdx.x < 64) windows_compute<STATS, SERVE>(P, mail, lane);
-    else windows_write<STATS, SERVE>(P, mail, lane);
+    __shared__ u64 shared[2 * kWaveLdsBytes / 8];
+    static_assert(sizeof(LaneMail) <= sizeof(shared), "layout");
+    const int lane = threadIdx.x & 63, wave = uniform((int)(threadIdx.x >> 6));
+    uint8_t* lev = reinterpret_cast<uint8_t*>(shared) + wave * kWaveLdsBytes;
+    const LaneShare share = lane_share<SERVE>(P);
+    if constexpr (SERVE) {
+        if (share.n <= 2ull * gridDim.x) {
+            windows_few(P, lev, share.n_hot, (uint32_t)share.n, (uint32_t)blockIdx.x + (uint32_t)wave * gridDim.x,
+                        2u * gridDim.x, lane);
+            return;
+        }
+    } else if ((int)blockIdx.x < P.long_blocks) {
+        windows_long<STATS>(P, lev, (uint64_t)blockIdx.x * 2 + wave, lane);
+        return;
+    }
+    LaneMail& mail = *reinterpret_cast<LaneMail*>(shared);
+    if (wave == 0) windows_compute<STATS, SERVE>(P, share, mail, lane);
+    else windows_write<STATS, SERVE>(P, share, mail, lane);
 }
 
 // ---------------------------------------------------------------------------

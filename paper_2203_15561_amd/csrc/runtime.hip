@@ -435,6 +435,15 @@ int align_lanes(genasm_ctx* ctx, AlignParams p, const genasm_launch& L, uint64_t
     p.pair_lanes = 1;
     while (p.pair_lanes < 64 && (uint64_t)ctx->num_cus * 2 * p.pair_lanes < p.n_pairs) p.pair_lanes *= 2;
     const uint64_t max_blocks = (uint64_t)ctx->num_cus * L.workers_per_cu;
+    if (L.lpt_order && max_blocks == 0) {
+        // A batch ends with its longest chains of windows, and a wavefront of its
+        // own runs a chain of related bases in 2 us a window, a lane in 5: the
+        // longest pairs, at most one per compute unit, start on those (50,000
+        // uneven pairs: windows 4.87 -> 4.35 ms; twice as many gain nothing there
+        // and cost 20,000 pairs of 10 kb 1.82 -> 2.21 ms).
+        p.long_pairs = (int)std::min<uint64_t>(p.n_pairs / 16, (uint64_t)ctx->num_cus);
+        p.long_blocks = (p.long_pairs + 1) / 2;
+    }
     CHECK_HIP(ctx, mark(0));
     CHECK_HIP(ctx, launch_lane_prep(p, total_read_bases, total_ref_bases, s));
     if (L.lpt_order) {

@@ -26,7 +26,7 @@
 
 constexpr int kBandBelow = 21;
 constexpr int kNoCell = 0x4000;    // f of a diagonal without a cell at that level, or near it
-// A diagonal's levels 0..64 (and up to 3 computed past them), one byte each, side by side: only its
+// A diagonal's levels 0..64 (and one computed past them), one byte each, side by side: only its
 // lane writes and reads them, four at a time on the way back (17 words apart,
 // so the lanes' words lie in different banks).
 constexpr int kWaveLevels = 68;
@@ -39,6 +39,35 @@ __device__ __forceinline__ int read_lane(int v, int lane) {
     return __builtin_amdgcn_readlane(v, lane);
 #else
     return __shfl(v, lane);
+#endif
+}
+__device__ __forceinline__ uint32_t write_lane(uint32_t old, uint32_t v, int at, int lane) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    (void)lane;
+    asm("v_writelane_b32 %0, %1, %2" : "+v"(old) : "s"(v), "{m0}"(at));
+    return old;
+#else
+    return lane == at ? v : old;
+#endif
+}
+// Bits of a field (its first bit, and its width << 16) of v.
+__device__ __forceinline__ int bit_field(int v, uint32_t field) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    int r;
+    asm("s_bfe_u32 %0, %1, %2" : "=s"(r) : "s"(v), "s"(field) : "scc");
+    return r;
+#else
+    return (int)(((uint32_t)v >> (field & 31u)) & ((1u << (field >> 16)) - 1u));
+#endif
+}
+// Zeros below the lowest set bit, 64 or more when there is none.
+__device__ __forceinline__ uint32_t trailing_zeros(u64 v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    int r;
+    asm("s_ff1_i32_b64 %0, %1" : "=s"(r) : "s"(v));  // -1 for 0
+    return (uint32_t)r;
+#else
+    return v ? (uint32_t)__builtin_ctzll(v) : ~0u;
 #endif
 }
 // The next (previous) lane's value; the last (first) lane gets `edge`.
@@ -147,9 +176,9 @@ __device__ __forceinline__ int wave_levels(const WaveWindow<SETS>& w, uint8_t* l
 #pragma unroll
     for (int s = 0; s < SETS; ++s) out[s] = lev + (64 * s + lane) * kWaveLevels;
     // matches before text base f, then the level's byte (of a diagonal without a
-    // cell a number that stays far above 64 over 65 levels); whether it reaches
-    // (0, 0)
-    auto extend = [&](int d) -> bool {
+    // cell a number that stays far above 64 over 66 levels); returns -f of (0, 0)'s
+    // diagonal, 0 when the level reaches it
+    auto extend = [&](int d) -> int {
 #pragma unroll
         for (int s = 0; s < SETS; ++s) {
             const u64 x = w.ne[s] << (g[s] & 63);
@@ -157,28 +186,28 @@ __device__ __forceinline__ int wave_levels(const WaveWindow<SETS>& w, uint8_t* l
             g[s] += (int)run;
             out[s][d] = (uint8_t)min((uint32_t)-g[s], 255u);
         }
-        return read_lane(g[below / 64], below & 63) == 0;
+        return read_lane(g[below / 64], below & 63);
     };
-    auto level = [&](int d) -> bool {  // d > 0: from the level before
+    auto level = [&](int d) -> int {  // d > 0: from the level before
         int up[SETS], dn[SETS];
 #pragma unroll
         for (int s = 0; s < SETS; ++s) {
             up[s] = lane_above(g[s], s + 1 < SETS ? read_lane(g[s + 1 < SETS ? s + 1 : s], 0) : -kNoCell, lane);
-            dn[s] = lane_below(g[s], s > 0 ? read_lane(g[s > 0 ? s - 1 : s], 63) : -kNoCell, lane);
+            dn[s] = lane_below(g[s] + 1, s > 0 ? read_lane(g[s > 0 ? s - 1 : s], 63) + 1 : -kNoCell, lane);
         }
 #pragma unroll
-        for (int s = 0; s < SETS; ++s) g[s] = min(max(max(g[s], dn[s]) + 1, up[s]), first[s]);
+        for (int s = 0; s < SETS; ++s) g[s] = min(max(max(g[s] + 1, dn[s]), up[s]), first[s]);
         return extend(d);
     };
-    if (extend(0)) return 0;
-    int d = 1;
-    for (; d <= d_max; d += 4) {
-        if (level(d)) break;
-        if (level(d + 1)) { d += 1; break; }
-        if (level(d + 2)) { d += 2; break; }
-        if (level(d + 3)) { d += 3; break; }
+    if (extend(0) == 0) return 0;
+    // two levels a turn, so that the first one's answer is read while the second
+    // is computed
+    for (int d = 1; d <= d_max; d += 2) {
+        const int a = level(d), b = level(d + 1);
+        if (a == 0) return d;
+        if (b == 0) return d < d_max ? d + 1 : -1;
     }
-    return d <= d_max ? d : -1;
+    return -1;
 }
 
 // The runs of a pair's CIGAR, the same in every lane.
@@ -244,26 +273,28 @@ __device__ __forceinline__ int wave_trace(const WaveWindow<SETS>& w, const uint8
         return *reinterpret_cast<const int*>(lev + (64 * s + lane) * kWaveLevels + (max(level, 0) & ~3));
     };
     int i = 0, x = below;  // text base and diagonal index: read base j = i + x - below
-    int n = 0, tail = 0;
-    int edit = -1;         // lane e: edit e's matches before it << 2 | op
-    int level = d - 1;     // the one the next edit asks
+    int n = 0, tail;
+    uint32_t edit = 0u;    // lane e: edit e's matches before it << 2 | op
+    int level = d - 1;     // the one the next edit asks: byte level % 4 of f
+    uint32_t field = (uint32_t)(8 * (level & 3)) | (8u << 16);  // that byte, as a bit field
     int f[SETS], next[SETS];
 #pragma unroll
     for (int s = 0; s < SETS; ++s) {
         f[s] = load(level, s);
         next[s] = load(level - 4, s);
     }
+    // i + j grows with every edit, so the loop ends
     for (;;) {
-        const int limit = min(i_max, j_max + below - x);  // the diagonal's last committed text base + 1
+        const int limit = min(i_max, j_max + below - x) - i;  // matches to the diagonal's last committed cell
         u64 ne = 0;
 #pragma unroll
         for (int s = 0; s < SETS; ++s)
             if (SETS == 1 || (x >> 6) == s)
                 ne = ((u64)(uint32_t)read_lane((int)(w.ne[s] >> 32), x & 63) << 32) |
                      (uint32_t)read_lane((int)w.ne[s], x & 63);
-        const int k = min(ctz64(ne >> (i & 63)), limit - i);
+        const int k = (int)min(trailing_zeros(ne >> (i & 63)), (uint32_t)limit);
         i += k;
-        if (i >= limit || level < 0) {
+        if (k == limit) {
             tail = k;
             break;
         }
@@ -273,27 +304,26 @@ __device__ __forceinline__ int wave_trace(const WaveWindow<SETS>& w, const uint8
             if (SETS == 1 || (x >> 6) == s) fs = read_lane(f[s], x & 63);
             if (SETS == 1 || ((x + 1) >> 6) == s) fi = read_lane(f[s], (x + 1) & 63);
         }
-        const int at = 8 * (level & 3);
-        fs = (int)((uint32_t)fs >> at) & 255;
-        fi = (int)((uint32_t)fi >> at) & 255;
         // the op, and what it adds to the text base (bit 2) and to the diagonal (from bit 3)
-        int e = fi <= i ? (int)GENASM_OP_INS | 8 : (int)GENASM_OP_DEL | 4 | -8;
-        e = fs <= i + 1 ? (int)GENASM_OP_MISMATCH | 4 : e;
-        if (lane == n) edit = (k << 2) | (e & 3);
+        int e = bit_field(fi, field) <= i ? (int)GENASM_OP_INS | 8 : (int)GENASM_OP_DEL | 4 | -8;
+        e = bit_field(fs, field) <= i + 1 ? (int)GENASM_OP_MISMATCH | 4 : e;
+        edit = write_lane(edit, ((uint32_t)k << 2) | (uint32_t)(e & 3), n, lane);
         ++n;
         i += (e >> 2) & 1;
         x += e >> 3;
-        if (at == 0) {
+        field -= 8u;
+        --level;
+        if ((int)(field << 16) < 0) {  // below byte 0
+            field += 32u;
 #pragma unroll
             for (int s = 0; s < SETS; ++s) {
                 f[s] = next[s];
-                next[s] = load(level - 5, s);
+                next[s] = load(level - 4, s);
             }
         }
-        --level;
     }
     const int j = i + x - below;
-    if (n > 0) wave_edits(runs, n, edit >> 2, edit & 3, lane);
+    if (n > 0) wave_edits(runs, n, (int)(edit >> 2), (int)(edit & 3u), lane);
     if (tail > 0) wave_run(runs, (int)GENASM_OP_MATCH, tail, lane);
     // past the text only insertions are left
     const int rest = i < L && j < j_max ? j_max - j : 0;
@@ -352,52 +382,26 @@ __device__ __forceinline__ u64 wave_search(const AlignParams& P, const PairCurso
     return (int)(key >> 32) <= Kr ? key : ~0ull;
 }
 
-template <bool STATS>
-__global__ __launch_bounds__(64) void k_pair_wave(AlignParams P) {
-    extern __shared__ u64 smem[];
-    const int lane = threadIdx.x & 63;
-    const uint64_t pair = blockIdx.x;
-    if (pair >= P.n_pairs) return;
-    PairCursor pc = pair_cursor(P, pair);
-    pc.rb = uniform64(pc.rb);
-    pc.fb = uniform64(pc.fb);
-    pc.m = uniform(pc.m);
-    pc.n = uniform(pc.n);
-    if (pc.m == 0) {
-        if (lane == 0) finish_without_windows(P, pair, 0);
-        return;
-    }
-    uint8_t* lev = reinterpret_cast<uint8_t*>(smem);
-    WaveSeq rd, rf;
-    u64 pl, ph, tl, th;
-    wave_seq_open(rd, P.reads, pc.rb, pc.m, 0, lane);
-    wave_seq_window(rd, 0, lane, pl, ph);
-    const int m1 = min(P.W, pc.m);
-    const int Kr = min(P.K, m1 - 1);
-    const u64 key = wave_search(P, pc, m1, Kr, pl, ph, lane);
-    int row = -1, col = 0;
-    if (key != ~0ull) {
-        row = (int)(key >> 32);
-        col = (int)(uint32_t)key;
-    } else if (m1 <= P.K) {
-        row = m1;  // row m1 hits in every column
-    }
-    if (STATS && lane == 0) search_stats(P, pair, pc.n, m1, row >= 0 ? row : Kr, (u64)pc.n, true);
-    if (row < 0) {
-        if (lane == 0) finish_without_windows(P, pair, -1);
-        return;
-    }
+// The windows of a pair from the state `st` on, to its end or (serving) to the
+// end of its turn, and its result or state.
+template <bool STATS, bool SERVE>
+__device__ __forceinline__ void wave_pair_windows(const AlignParams& P, uint64_t pair, const PairCursor& pc, int col,
+                                                  PairState st, uint8_t* lev, int lane, TurnClock& turn) {
     const uint64_t base = uniform64(pair_run_base(P, pair));
     const uint64_t limit = min(P.cigar_cap, base + (uint64_t)pc.m + (uint64_t)pc.n);
-    WaveRuns runs{-1, 0u, 0u, (uint32_t)uniform((int)(limit > base ? limit - base : 0ull)), P.cigar + base};
-    wave_seq_open(rf, P.refs, pc.fb, pc.n, col, lane);
-    int ti = col, pj = 0, score = 0;
-    uint32_t nwin = 0;
-    bool failed = false, internal = false;
+    WaveRuns runs{st.cur_op, st.cur_len, st.written,
+                  (uint32_t)uniform((int)(limit > base ? limit - base : 0ull)), P.cigar + base};
+    WaveSeq rd, rf;
+    u64 pl, ph, tl, th;
+    int ti = st.ti, pj = st.pj, score = st.score;
+    uint32_t nwin = st.nwin, done_here = 0u;
+    wave_seq_open(rd, P.reads, pc.rb, pc.m, pj, lane);
+    wave_seq_open(rf, P.refs, pc.fb, pc.n, ti, lane);
+    bool failed = false, internal = false, park = false;
     u64 st_wops = 0, st_cells = 0, st_table = 0, st_tb = 0, st_steps = 0;
     // every window commits at least one base, so a pair has at most m + n
     const uint32_t max_windows = (uint32_t)pc.m + (uint32_t)pc.n;
-    while (pj < pc.m) {
+    while (pj < pc.m && !park) {
         if (nwin >= max_windows) {
             failed = internal = true;
             break;
@@ -408,6 +412,7 @@ __global__ __launch_bounds__(64) void k_pair_wave(AlignParams P) {
             break;
         }
         ++nwin;
+        ++done_here;
         wave_seq_window(rd, pj, lane, pl, ph);
         wave_seq_window(rf, ti, lane, tl, th);
         int edits = 0, i_end = 0, j_end = 0, d;
@@ -437,22 +442,29 @@ __global__ __launch_bounds__(64) void k_pair_wave(AlignParams P) {
         score += edits;
         ti += i_end;
         pj += j_end;
+        if constexpr (SERVE) {
+            // a turn takes at least one window and starts none once it has ended
+            park = pj < pc.m && ((turn.active && turn.over()) ||
+                                 (P.window_budget != 0u && done_here >= P.window_budget));
+        }
     }
     if (lane != 0) return;
-    if (!failed && runs.cur_op >= 0) {
-        wave_put(runs, runs.written, runs.cur_len, runs.cur_op);
-        ++runs.written;
+    if (!park) {
+        if (!failed && runs.cur_op >= 0) {
+            wave_put(runs, runs.written, runs.cur_len, runs.cur_op);
+            ++runs.written;
+        }
+        const bool overflow = runs.written > runs.room;
+        genasm_result r;
+        r.edit_distance = failed ? -1 : score;
+        r.ref_begin = failed ? 0u : (uint32_t)col;
+        r.ref_end = failed ? 0u : (uint32_t)ti;
+        r.cigar_len = failed || overflow ? 0u : runs.written;
+        r.n_windows = nwin;
+        r.cigar_off = base;
+        r.flags = (overflow && !failed ? GENASM_FLAG_CIGAR_OVERFLOW : 0u) | (internal ? GENASM_FLAG_INTERNAL : 0u);
+        P.out[pair] = r;
     }
-    const bool overflow = runs.written > runs.room;
-    genasm_result r;
-    r.edit_distance = failed ? -1 : score;
-    r.ref_begin = failed ? 0u : (uint32_t)col;
-    r.ref_end = failed ? 0u : (uint32_t)ti;
-    r.cigar_len = failed || overflow ? 0u : runs.written;
-    r.n_windows = nwin;
-    r.cigar_off = base;
-    r.flags = (overflow && !failed ? GENASM_FLAG_CIGAR_OVERFLOW : 0u) | (internal ? GENASM_FLAG_INTERNAL : 0u);
-    P.out[pair] = r;
     if constexpr (STATS) {
         u64* stp = P.stats + pair * kStatCount;
         stp[kStatWindowWordOps] += st_wops;
@@ -461,5 +473,90 @@ __global__ __launch_bounds__(64) void k_pair_wave(AlignParams P) {
         stp[kStatTbReads] += st_tb;
         stp[kStatWindowLaneSteps] += st_steps;
         stp[kStatWindows] += nwin;
+    }
+    if constexpr (SERVE) {
+        P.state[pair] = PairState{ti, pj, score, nwin, runs.written, runs.cur_op, runs.cur_len,
+                                  kStateStarted | (park ? 0u : kStateDone) | (failed ? kStateFailed : 0u) |
+                                      (internal ? kStateInternal : 0u)};
+        if (P.fin_list) {
+            if (!park) P.fin_list[atomicAdd(P.fin_len, 1u)] = (uint32_t)pair;
+            else if (done_here <= 1u) P.next_hot[atomicAdd(P.next_len + kCounterEasyLen, 1u)] = (uint32_t)pair;
+            else P.next_cold[atomicAdd(P.next_len + kCounterHardLen, 1u)] = (uint32_t)pair;
+        }
+    }
+}
+
+__device__ __forceinline__ PairCursor wave_cursor(const AlignParams& P, uint64_t pair) {
+    PairCursor pc = pair_cursor(P, pair);
+    pc.rb = uniform64(pc.rb);
+    pc.fb = uniform64(pc.fb);
+    pc.m = uniform(pc.m);
+    pc.n = uniform(pc.n);
+    return pc;
+}
+
+template <bool STATS>
+__global__ __launch_bounds__(64) void k_pair_wave(AlignParams P) {
+    extern __shared__ u64 smem[];
+    const int lane = threadIdx.x & 63;
+    const uint64_t pair = blockIdx.x;
+    if (pair >= P.n_pairs) return;
+    const PairCursor pc = wave_cursor(P, pair);
+    if (pc.m == 0) {
+        if (lane == 0) finish_without_windows(P, pair, 0);
+        return;
+    }
+    WaveSeq rd;
+    u64 pl, ph;
+    wave_seq_open(rd, P.reads, pc.rb, pc.m, 0, lane);
+    wave_seq_window(rd, 0, lane, pl, ph);
+    const int m1 = min(P.W, pc.m);
+    const int Kr = min(P.K, m1 - 1);
+    const u64 key = wave_search(P, pc, m1, Kr, pl, ph, lane);
+    int row = -1, col = 0;
+    if (key != ~0ull) {
+        row = (int)(key >> 32);
+        col = (int)(uint32_t)key;
+    } else if (m1 <= P.K) {
+        row = m1;  // row m1 hits in every column
+    }
+    if (STATS && lane == 0) search_stats(P, pair, pc.n, m1, row >= 0 ? row : Kr, (u64)pc.n, true);
+    if (row < 0) {
+        if (lane == 0) finish_without_windows(P, pair, -1);
+        return;
+    }
+    TurnClock none;
+    wave_pair_windows<STATS, false>(P, pair, pc, col, fresh_state(col), reinterpret_cast<uint8_t*>(smem), lane, none);
+}
+
+// The window kernel's wavefronts that take a pair each (see k_windows_lane): one
+// of the longest pairs of a batch, or (serving) a share of the resident pairs.
+template <bool STATS>
+__device__ __forceinline__ void windows_long(const AlignParams& P, uint8_t* lev, uint64_t at, int lane) {
+    if (at >= (uint64_t)P.long_pairs) return;
+    const uint64_t pair = P.order[at];
+    if (search_outcome(P, pair) < 0) return;  // the same in every lane
+#if defined(GENASM_DEBUG)
+    if (P.audit && lane == 0) atomicAdd(P.audit + pair, kAuditTake);  // queue audit
+#endif
+    const int col = uniform((int)P.search[pair].col);
+    TurnClock none;
+    wave_pair_windows<STATS, false>(P, pair, wave_cursor(P, pair), col, fresh_state(col), lev, lane, none);
+}
+
+__device__ __forceinline__ void windows_few(const AlignParams& P, uint8_t* lev, uint32_t n_hot, uint32_t n,
+                                            uint32_t first, uint32_t stride, int lane) {
+    TurnClock turn;
+    turn.open(P);
+    for (uint32_t at = first; at < n; at += stride) {
+        const uint64_t pair = (uint32_t)uniform((int)(at < n_hot ? P.easy_list[at] : P.hard_list[at - n_hot]));
+        const int row = uniform(P.search[pair].row), col = uniform((int)P.search[pair].col);
+        const PairState s = P.state[pair];
+        PairState st{uniform(s.ti), uniform(s.pj), uniform(s.score), (uint32_t)uniform((int)s.nwin),
+                     (uint32_t)uniform((int)s.written), uniform(s.cur_op), (uint32_t)uniform((int)s.cur_len),
+                     (uint32_t)uniform((int)s.flags)};
+        if (row < 0 || (st.flags & kStateDone)) continue;
+        if (!(st.flags & kStateStarted)) st = fresh_state(col);
+        wave_pair_windows<false, true>(P, pair, wave_cursor(P, pair), col, st, lev, lane, turn);
     }
 }
