@@ -437,7 +437,7 @@ int align_lanes(genasm_ctx* ctx, AlignParams p, const genasm_launch& L, uint64_t
     const uint64_t max_blocks = (uint64_t)ctx->num_cus * L.workers_per_cu;
     if (L.lpt_order && max_blocks == 0) {
         // A batch ends with its longest chains of windows, and a wavefront of its
-        // own runs a chain of related bases in 2 us a window, a lane in 5: the
+        // own runs a chain of related bases in 1.7 us a window, a lane in 5: the
         // longest pairs, at most one per compute unit, start on those (50,000
         // uneven pairs: windows 4.87 -> 4.35 ms; twice as many gain nothing there
         // and cost 20,000 pairs of 10 kb 1.82 -> 2.21 ms).

@@ -12,9 +12,11 @@
 // for approximate string matching, 1985, from the end and with a free text
 // end.) d* is the first level that reaches (0, 0). The traceback asks for E of
 // neighbouring cells against d - 1 only, which is f_d-1 of their diagonals. A
-// level costs about 20 instructions, so a window costs by its distance: about
-// 2 us at d* = 6 and 5 us at d* = 33, where a lane's column-by-column step
-// (diff_window.h) takes 5 us, for up to 64 pairs at once.
+// level costs 14 instructions, about 90 cycles of a wavefront that has its SIMD
+// to itself, and an edit of the traceback 31 scalar ones, so a window costs by
+// its distance: about 1.7 us at d* = 6 and 4.4 us at d* = 33 (unrelated bases),
+// where a lane's column-by-column step (diff_window.h) takes 5 us, for up to 64
+// pairs at once. 67 reads of 30 kb: 15.1 ms in row tables -> 2.6.
 //
 // An alignment of d edits from (0, 0) stays on diagonals -(d + nw - mw) / 2 .. d:
 // past -x it needs x deletions, and then x + mw - nw insertions to reach the
@@ -25,7 +27,6 @@
 #include "diff_window.h"
 
 constexpr int kBandBelow = 21;
-constexpr int kNoCell = 0x4000;    // f of a diagonal without a cell at that level, or near it
 // A diagonal's levels 0..64 (and one computed past them), one byte each, side by side: only its
 // lane writes and reads them, four at a time on the way back (17 words apart,
 // so the lanes' words lie in different banks).
@@ -41,6 +42,15 @@ __device__ __forceinline__ int read_lane(int v, int lane) {
     return __shfl(v, lane);
 #endif
 }
+__device__ __forceinline__ u64 read_lane64(u64 v, int lane) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    // built from its halves, which two shifts and an or would cost moves for
+    typedef uint32_t halves __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(u64, halves{(uint32_t)read_lane((int)v, lane), (uint32_t)read_lane((int)(v >> 32), lane)});
+#else
+    return ((u64)(uint32_t)read_lane((int)(v >> 32), lane) << 32) | (uint32_t)read_lane((int)v, lane);
+#endif
+}
 __device__ __forceinline__ uint32_t write_lane(uint32_t old, uint32_t v, int at, int lane) {
 #if defined(__HIP_DEVICE_COMPILE__)
     (void)lane;
@@ -48,16 +58,6 @@ __device__ __forceinline__ uint32_t write_lane(uint32_t old, uint32_t v, int at,
     return old;
 #else
     return lane == at ? v : old;
-#endif
-}
-// Bits of a field (its first bit, and its width << 16) of v.
-__device__ __forceinline__ int bit_field(int v, uint32_t field) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    int r;
-    asm("s_bfe_u32 %0, %1, %2" : "=s"(r) : "s"(v), "s"(field) : "scc");
-    return r;
-#else
-    return (int)(((uint32_t)v >> (field & 31u)) & ((1u << (field >> 16)) - 1u));
 #endif
 }
 // Zeros below the lowest set bit, 64 or more when there is none.
@@ -83,6 +83,19 @@ __device__ __forceinline__ int lane_above(int v, int edge, int lane) {
 __device__ __forceinline__ int lane_below(int v, int edge, int lane) {
     (void)lane;
     return __builtin_amdgcn_update_dpp(edge, v, kDppWaveShr1, 0xF, 0xF, false);
+}
+// The same with 0 at the edge.
+__device__ __forceinline__ int lane_above0(int v, int lane) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    (void)lane;
+    return __builtin_amdgcn_update_dpp(0, v, 0x130 /* wave_shl:1 */, 0xF, 0xF, true);
+#else
+    return lane_above(v, 0, lane);
+#endif
+}
+__device__ __forceinline__ int lane_below0(int v, int lane) {
+    (void)lane;
+    return __builtin_amdgcn_update_dpp(0, v, kDppWaveShr1, 0xF, 0xF, true);
 }
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ u64 uniform64(u64 v) {
@@ -139,52 +152,65 @@ __device__ __forceinline__ void wave_seq_window(WaveSeq& q, int at, int lane, u6
     hi = funnel64(q.hi0, q.hi1, at & 63);
 }
 
-// The diagonals of a window: lane l of set s holds diagonal 64 s + l - below.
+// The diagonals of a window: lane l of set s holds diagonal t = 64 s + l - below
+// (text base i with read base j = i + t). A diagonal's cells are numbered from
+// its first one: a = min(i, j), so all words and levels start at 0. Behind the
+// text the diagonals go on with cells that always differ, up to the read
+// window's end: an edit there costs what the insertion it stands for does, so
+// no distance changes, and every diagonal that can be used has a level 0.
 template <int SETS> struct WaveWindow {
     static constexpr int below = SETS == 1 ? kBandBelow : 63;  // two sets: -63 .. 64
-    u64 ne[SETS];  // bit i: text base i and the diagonal's read base differ, or there is no such cell
+    u64 ne[SETS];  // bit a: the bases of the diagonal's cell a differ
 };
 
 template <int SETS>
-__device__ __forceinline__ void wave_window(WaveWindow<SETS>& w, u64 pl, u64 ph, u64 tl, u64 th, int lane) {
+__device__ __forceinline__ void wave_window(WaveWindow<SETS>& w, u64 pl, u64 ph, u64 tl, u64 th, int nw, int lane) {
+    const u64 text = nw < 64 ? ~(~0ull << nw) : ~0ull;
 #pragma unroll
     for (int s = 0; s < SETS; ++s) {
         const int t = 64 * s + lane - WaveWindow<SETS>::below;
-        const int r = max(t, 0) & 63, l = max(-t, 0);
-        const u64 m = l >= 64 ? ~0ull : ~(~0ull << l);  // cells before the read window's start
-        const u64 a = (pl >> r) << (l & 63), b = (ph >> r) << (l & 63);
-        w.ne[s] = (a ^ tl) | (b ^ th) | m;
+        const int r = max(t, 0) & 63, l = max(-t, 0);  // diagonal 64 has no cell to compare
+        w.ne[s] = ((pl >> r) ^ (tl >> l)) | ((ph >> r) ^ (th >> l)) | ~(text >> l);
     }
 }
 
+// Zeros above the highest set bit, and at most `most`.
+__device__ __forceinline__ int leading_zeros(u64 v, int most) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    uint32_t h, l;  // ~0 for 0
+    asm("v_ffbh_u32 %0, %1" : "=v"(h) : "v"((uint32_t)(v >> 32)));
+    asm("v_ffbh_u32 %0, %1" : "=v"(l) : "v"((uint32_t)v));
+    return (int)min(min(h, __builtin_elementwise_add_sat(l, 32u)), (uint32_t)most);
+#else
+    return v ? min(__builtin_clzll(v), most) : most;
+#endif
+}
+
 // Levels 0.. into lev; returns the first that reaches (0, 0), or -1 when none up
-// to d_max does.
+// to d_max does. A level's f is held as g = 64 - f: the shift that brings the
+// cell before f to the top (modulo 64), 0 for a diagonal beyond the band, whose
+// neighbours learn nothing from it.
 template <int SETS>
-__device__ __forceinline__ int wave_levels(const WaveWindow<SETS>& w, uint8_t* lev, int mw, int nw, int d_max,
-                                           int lane) {
+__device__ __forceinline__ int wave_levels(const WaveWindow<SETS>& w, uint8_t* lev, int mw, int d_max, int lane) {
     constexpr int below = WaveWindow<SETS>::below;
-    // f negated, so that it is the extension's shift count (modulo 64) as it is
-    int g[SETS], first[SETS];
+    int g[SETS], above[SETS], under[SETS];
+    uint8_t* out[SETS];
 #pragma unroll
     for (int s = 0; s < SETS; ++s) {
         const int t = 64 * s + lane - below;
-        first[s] = min(t, 0);
-        // the read window's end, where the diagonal reaches it inside the text
-        g[s] = mw - t >= -first[s] && mw - t <= nw ? t - mw : -kNoCell;
+        g[s] = min(64 - mw + max(t, 0), 64);
+        // a step away from the main diagonal's side shortens a by one
+        above[s] = t < 0;
+        under[s] = t > 0;
+        out[s] = lev + (64 * s + lane) * kWaveLevels;
     }
-    uint8_t* out[SETS];
-#pragma unroll
-    for (int s = 0; s < SETS; ++s) out[s] = lev + (64 * s + lane) * kWaveLevels;
-    // matches before text base f, then the level's byte (of a diagonal without a
-    // cell a number that stays far above 64 over 66 levels); returns -f of (0, 0)'s
-    // diagonal, 0 when the level reaches it
+    // matches before cell f, then the level's byte; returns g of (0, 0)'s
+    // diagonal, 64 when the level reaches it
     auto extend = [&](int d) -> int {
 #pragma unroll
         for (int s = 0; s < SETS; ++s) {
-            const u64 x = w.ne[s] << (g[s] & 63);
-            const uint32_t run = min((uint32_t)(x ? __builtin_clzll(x) : 64), (uint32_t)-g[s]);
-            g[s] += (int)run;
-            out[s][d] = (uint8_t)min((uint32_t)-g[s], 255u);
+            g[s] += leading_zeros(w.ne[s] << (g[s] & 63), 64 - g[s]);
+            out[s][d] = (uint8_t)g[s];
         }
         return read_lane(g[below / 64], below & 63);
     };
@@ -192,22 +218,25 @@ __device__ __forceinline__ int wave_levels(const WaveWindow<SETS>& w, uint8_t* l
         int up[SETS], dn[SETS];
 #pragma unroll
         for (int s = 0; s < SETS; ++s) {
-            up[s] = lane_above(g[s], s + 1 < SETS ? read_lane(g[s + 1 < SETS ? s + 1 : s], 0) : -kNoCell, lane);
-            dn[s] = lane_below(g[s] + 1, s > 0 ? read_lane(g[s > 0 ? s - 1 : s], 63) + 1 : -kNoCell, lane);
+            up[s] = s + 1 < SETS ? lane_above(g[s], read_lane(g[s + 1 < SETS ? s + 1 : s], 0), lane)
+                                 : lane_above0(g[s], lane);
+            dn[s] = s > 0 ? lane_below(g[s], read_lane(g[s > 0 ? s - 1 : s], 63), lane) : lane_below0(g[s], lane);
         }
 #pragma unroll
-        for (int s = 0; s < SETS; ++s) g[s] = min(max(max(g[s] + 1, dn[s]), up[s]), first[s]);
+        for (int s = 0; s < SETS; ++s) g[s] = min(max(max(g[s] + 1, dn[s] + under[s]), up[s] + above[s]), 64);
         return extend(d);
     };
-    if (extend(0) == 0) return 0;
+    if (extend(0) == 64) return 0;
+    if (d_max < 1) return -1;
     // two levels a turn, so that the first one's answer is read while the second
-    // is computed
-    for (int d = 1; d <= d_max; d += 2) {
-        const int a = level(d), b = level(d + 1);
-        if (a == 0) return d;
-        if (b == 0) return d < d_max ? d + 1 : -1;
-    }
-    return -1;
+    // is computed; what has reached (0, 0) stays there
+    int d = 1, first, second;
+    do {
+        first = level(d);
+        second = level(d + 1);
+        d += 2;
+    } while (second != 64 && d <= d_max);
+    return first == 64 ? d - 2 : second == 64 && d - 1 <= d_max ? d - 1 : -1;
 }
 
 // The runs of a pair's CIGAR, the same in every lane.
@@ -231,11 +260,23 @@ __device__ __forceinline__ void wave_run(WaveRuns& r, int op, int len, int lane)
     r.cur_len += (uint32_t)len;
 }
 
-// Appends a window's edits, one per lane (lane e < n: the matches before the
-// edit and its op), all at once: an edit starts a run unless it follows one of
-// the same op without a match between; a run's place is the number of runs
-// before it and its length the distance to the next start.
-__device__ __forceinline__ void wave_edits(WaveRuns& r, int n, int matches, int op, int lane) {
+// An edit of a traceback: the text base it stands at, its op, and what it adds
+// to the text base and (the signed rest) to the diagonal.
+constexpr int kEditOp = 6, kEditText = 8, kEditDiag = 9;
+constexpr int kEditSub = (int)GENASM_OP_MISMATCH << kEditOp | 1 << kEditText;
+constexpr int kEditIns = (int)GENASM_OP_INS << kEditOp | 1 << kEditDiag;
+constexpr int kEditDel = (int)GENASM_OP_DEL << kEditOp | 1 << kEditText | -(1 << kEditDiag);
+
+// Appends a window's n edits, one per lane, all at once: an edit starts a run
+// unless it follows one of the same op without a match between; a run's place
+// is the number of runs before it and its length the distance to the next start.
+__device__ __forceinline__ void wave_edits(WaveRuns& r, int n, int edit, int lane) {
+    const int op = (edit >> kEditOp) & 3, i = edit & 63;
+    // behind the edit before; kept out of the subtraction, since the reversed
+    // subtraction it would be folded into as its shifted operand gives the
+    // negative result here
+    const int after = (int)here((uint32_t)lane_below0(i + ((edit >> kEditText) & 1), lane));
+    const int matches = i - after;
     const bool have = lane < n;
     const int before = lane_below(op, -1, lane);
     const bool m = have && matches > 0, start = have && (matches > 0 || op != before);
@@ -263,67 +304,86 @@ __device__ __forceinline__ void wave_edits(WaveRuns& r, int n, int matches, int 
 
 // Traceback of a window of distance d from (0, 0); returns the edits it
 // commits. Each edit lowers d by one, so the levels are read in order, four to a
-// word and a word ahead of its use.
+// word, and the word after the next is on its way.
 template <int SETS>
 __device__ __forceinline__ int wave_trace(const WaveWindow<SETS>& w, const uint8_t* lev, int mw, int nw, int d,
                                           int L, int lane, WaveRuns& runs, int& i_end, int& j_end) {
     constexpr int below = WaveWindow<SETS>::below;
     const int j_max = min(mw, L), i_max = min(L, nw);
-    auto load = [&](int level, int s) -> int {
-        return *reinterpret_cast<const int*>(lev + (64 * s + lane) * kWaveLevels + (max(level, 0) & ~3));
+    int level = d - 1;  // the one the next edit asks
+    const int lead = 8 * (3 - (level & 3));  // so that it is the top byte of its word
+    u64 ne[SETS];       // bit i of it: text base i and the diagonal's read base differ
+    int last[SETS];     // the diagonal's last committed text base, and one more
+    uint32_t f64[SETS], word[SETS], next[SETS];
+    uint32_t f[SETS], fi[SETS];  // four levels' first text bases, here and on the next diagonal
+    auto load = [&](int at, int s) -> uint32_t {
+        return *reinterpret_cast<const uint32_t*>(lev + (64 * s + lane) * kWaveLevels + (max(at, 0) & ~3));
     };
-    int i = 0, x = below;  // text base and diagonal index: read base j = i + x - below
-    int n = 0, tail;
-    uint32_t edit = 0u;    // lane e: edit e's matches before it << 2 | op
-    int level = d - 1;     // the one the next edit asks: byte level % 4 of f
-    uint32_t field = (uint32_t)(8 * (level & 3)) | (8u << 16);  // that byte, as a bit field
-    int f[SETS], next[SETS];
-#pragma unroll
-    for (int s = 0; s < SETS; ++s) {
-        f[s] = load(level, s);
-        next[s] = load(level - 4, s);
-    }
-    // i + j grows with every edit, so the loop ends
-    for (;;) {
-        const int limit = min(i_max, j_max + below - x) - i;  // matches to the diagonal's last committed cell
-        u64 ne = 0;
-#pragma unroll
-        for (int s = 0; s < SETS; ++s)
-            if (SETS == 1 || (x >> 6) == s)
-                ne = ((u64)(uint32_t)read_lane((int)(w.ne[s] >> 32), x & 63) << 32) |
-                     (uint32_t)read_lane((int)w.ne[s], x & 63);
-        const int k = (int)min(trailing_zeros(ne >> (i & 63)), (uint32_t)limit);
-        i += k;
-        if (k == limit) {
-            tail = k;
-            break;
-        }
-        int fs = 0, fi = 0;  // that level on this diagonal and the next
+    // a level of the word is the diagonal's first text base plus 64 - g; bytes
+    // above the level asked may be stale and don't reach those below
+    auto fields = [&] {
 #pragma unroll
         for (int s = 0; s < SETS; ++s) {
-            if (SETS == 1 || (x >> 6) == s) fs = read_lane(f[s], x & 63);
-            if (SETS == 1 || ((x + 1) >> 6) == s) fi = read_lane(f[s], (x + 1) & 63);
+            f[s] = (uint32_t)(((((u64)(f64[s] - word[s])) << 32 | (f64[s] - next[s])) << lead) >> 32);
+            word[s] = next[s];
+            next[s] = load(level - 8, s);
         }
-        // the op, and what it adds to the text base (bit 2) and to the diagonal (from bit 3)
-        int e = bit_field(fi, field) <= i ? (int)GENASM_OP_INS | 8 : (int)GENASM_OP_DEL | 4 | -8;
-        e = bit_field(fs, field) <= i + 1 ? (int)GENASM_OP_MISMATCH | 4 : e;
-        edit = write_lane(edit, ((uint32_t)k << 2) | (uint32_t)(e & 3), n, lane);
-        ++n;
-        i += (e >> 2) & 1;
-        x += e >> 3;
-        field -= 8u;
-        --level;
-        if ((int)(field << 16) < 0) {  // below byte 0
-            field += 32u;
 #pragma unroll
-            for (int s = 0; s < SETS; ++s) {
-                f[s] = next[s];
-                next[s] = load(level - 4, s);
-            }
-        }
+        for (int s = 0; s < SETS; ++s)
+            fi[s] = (uint32_t)lane_above((int)f[s], s + 1 < SETS ? read_lane((int)f[s + 1 < SETS ? s + 1 : s], 0) : -1,
+                                         lane);
+        level -= 4;
+    };
+#pragma unroll
+    for (int s = 0; s < SETS; ++s) {
+        const int t = 64 * s + lane - below, l = max(-t, 0);
+        ne[s] = w.ne[s] << l;
+        last[s] = min(i_max, j_max - t);
+        f64[s] = (uint32_t)(64 + l) * 0x01010101u;
+        word[s] = load(level, s);
+        next[s] = load(level - 4, s);
     }
+    int i = 0, x = below;  // text base and diagonal index: read base j = i + x - below
+    int n = 0;
+    int edit = 0;          // lane e: edit e
+    // the matches, and the edit after them unless they end at the diagonal's last
+    // committed cell (the next step inside, so that each has one branch)
+    auto step = [&](int byte, auto&& then) {
+        u64 differ = 0;
+        int end = 0, fs = 0, fn = 0;
+#pragma unroll
+        for (int s = 0; s < SETS; ++s)
+            if (SETS == 1 || (x >> 6) == s) {
+                differ = read_lane64(ne[s], x & 63);
+                end = read_lane(last[s], x & 63);
+                fs = read_lane((int)f[s], x & 63);
+                fn = read_lane((int)fi[s], x & 63);
+            }
+        // (at 64, the end of all, the mask is full)
+        i = max(i, (int)min(trailing_zeros(differ & (~0ull << (i & 63))), (uint32_t)end));
+        if (i == end) return;
+        int e = ((fn >> (8 * byte)) & 0xFF) <= i ? kEditIns : kEditDel;
+        e = ((fs >> (8 * byte)) & 0xFF) <= i + 1 ? kEditSub : e;
+        edit = (int)write_lane((uint32_t)edit, (uint32_t)(e | i), n, lane);
+        ++n;
+        i += (e >> kEditText) & 1;
+        x += e >> kEditDiag;
+        then();
+    };
+    // i + j grows with every edit, so the loop ends
+    bool more;
+    do {
+        fields();
+        more = false;
+        step(3, [&] { step(2, [&] { step(1, [&] { step(0, [&] { more = true; }); }); }); });
+    } while (more);
     const int j = i + x - below;
-    if (n > 0) wave_edits(runs, n, (int)(edit >> 2), (int)(edit & 3u), lane);
+    int tail = i;
+    if (n > 0) {
+        const int e = read_lane(edit, n - 1);
+        tail -= (e & 63) + ((e >> kEditText) & 1);
+        wave_edits(runs, n, edit, lane);
+    }
     if (tail > 0) wave_run(runs, (int)GENASM_OP_MATCH, tail, lane);
     // past the text only insertions are left
     const int rest = i < L && j < j_max ? j_max - j : 0;
@@ -339,9 +399,9 @@ __device__ __forceinline__ int wave_solve(u64 pl, u64 ph, u64 tl, u64 th, int mw
                                           uint8_t* lev, int lane, WaveRuns& runs, int& edits, int& i_end,
                                           int& j_end, bool& exact) {
     WaveWindow<SETS> w;
-    wave_window<SETS>(w, pl, ph, tl, th, lane);
+    wave_window<SETS>(w, pl, ph, tl, th, nw, lane);
     const int d_max = SETS == 1 ? min(K, 63 - kBandBelow) : K;
-    const int d = wave_levels<SETS>(w, lev, mw, nw, d_max, lane);
+    const int d = wave_levels<SETS>(w, lev, mw, d_max, lane);
     exact = SETS == 2;
     if (SETS == 1) {
         // no answer within K edits is one too when the band holds all of them
