@@ -131,8 +131,18 @@ struct WindowPath {
 // stands at (0 once it has left the read bases the window may commit).
 struct PathWalk {
     u64 cur, ins, sub;
-    uint32_t del[2];
+    uint32_t stay[2];  // columns that didn't move it, the latest in bit 0: 0..31 and 32..39
 };
+
+// bits << 1, and a set bit 0 if x is 0.
+__device__ __forceinline__ uint32_t shift_in_zero(uint32_t bits, u64 x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm("v_cmp_eq_u64_e32 vcc, 0, %1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(x) : "vcc");
+    return bits;
+#else
+    return (bits << 1) | (x == 0ull ? 1u : 0u);
+#endif
+}
 
 // One text column of the traceback: adding the position to the insertion cells
 // carries it over a run of them to the next other cell; a match or substitution
@@ -144,9 +154,9 @@ __device__ __forceinline__ void path_step(PathWalk& w, u64 U, u64 V, u64 live) {
     const u64 at = bit_op<kA & ~kB & kC>(sum, I, live);
     w.ins = bit_op<kA | (kB & ~kC)>(w.ins, I, sum);
     w.sub = bit_op<kA | (kB & kC)>(w.sub, at, U);
-    const u64 dv = at & V;
-    w.del[i / 32] |= (dv != 0ull ? 1u : 0u) << (i % 32);
-    w.cur = at + (at ^ dv);
+    const u64 move = at & ~V;
+    w.stay[i / 32] = shift_in_zero(w.stay[i / 32], move);
+    w.cur = at + move;
 }
 
 // The traceback's bits of a window: for column i, the cells of read bases 0..31
@@ -272,7 +282,15 @@ __device__ __forceinline__ WindowPath window_path(u64 pl, u64 ph, u64 tl, u64 th
     path_blocks<0>(p, t, live, L);
     w.ins = p.ins & live;
     w.sub = p.sub;
-    w.del = ((u64)p.del[1] << 32) | p.del[0];
+    // column i's bit back to bit i. A path that left its read bases stays at none
+    // from the column after its last move on (no deletion comes right before the
+    // insertions it may have left with).
+    const int tail = max(L - 32, 0);
+    u64 stay = ((u64)(tail ? reverse32(p.stay[1]) >> (32 - tail) : 0u) << 32) |
+               (reverse32(p.stay[0]) >> (32 - min(L, 32)));
+    const u64 moved = ~stay & (~0ull >> (64 - L));
+    if (p.cur == 0ull) stay &= moved ? ~0ull >> __builtin_clzll(moved) : 0ull;
+    w.del = stay;
     w.j_end = min(ctz64(p.cur), j_max);
     w.i_end = w.j_end - __builtin_popcountll(w.ins) + __builtin_popcountll(w.del);
     return w;

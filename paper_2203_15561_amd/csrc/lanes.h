@@ -26,23 +26,33 @@ __device__ __forceinline__ void close_run(RunOut& r) {
     ++r.written;
 }
 
+// A run of len > 0 ops; none of len 0. The run it closes goes to device memory.
 __device__ __forceinline__ void append_run(RunOut& r, int op, uint32_t len) {
-    if (len == 0u) return;
-    if (op != r.cur_op) {
-        if (r.cur_op >= 0) close_run(r);
-        r.cur_op = op;
-        r.cur_len = 0u;
-    }
-    r.cur_len += len;
+    const bool closes = len != 0u && op != r.cur_op;
+    if (closes && r.written < r.room) r.at[r.written] = (r.cur_len << 2) | (uint32_t)r.cur_op;
+    r.written += closes ? 1u : 0u;
+    r.cur_len = (closes ? 0u : r.cur_len) + len;
+    r.cur_op = len != 0u ? op : r.cur_op;
 }
 
 // Appends a window's path to the pair's runs, a run of matches and the run of
-// edits after it at a time; closed runs go to device memory. Within a window a
-// deletion is never next to an insertion or before a substitution (the earlier
-// of the two edges in the order S, I, D would have been valid a cell before),
-// so the next event in the read and the next in the text are never at the same
-// cell.
+// edits after it at a time. Within a window a deletion is never next to an
+// insertion or before a substitution (the earlier of the two edges in the order
+// S, I, D would have been valid a cell before), so the next event in the read
+// and the next in the text are never at the same cell.
+//
+// A wavefront takes as many turns as its lane with the most runs, about 30 with
+// unrelated pairs in the batch, and every branch costs it more than the few
+// instructions behind it: masks instead (20,000 pairs of 10 kb, 30% of them
+// unrelated: 15,800 -> 8,300 cycles a window, where the other wavefront takes
+// 11,600).
 __device__ __forceinline__ void append_path(u64 ins, u64 sub, u64 del, int j, int i, RunOut& r) {
+    constexpr int kDelOrIns = (int)GENASM_OP_MISMATCH;
+    static_assert(GENASM_OP_INS == kDelOrIns + 1 && GENASM_OP_DEL == kDelOrIns + 2, "ops in order");
+    // a pair's first run joins an empty one of its own op
+    if (r.cur_op < 0)
+        r.cur_op = del & 1u ? (int)GENASM_OP_DEL : ins & 1u ? (int)GENASM_OP_INS
+                   : sub & 1u ? (int)GENASM_OP_MISMATCH : (int)GENASM_OP_MATCH;
     for (int it = 0; it < 2 * kLaneCols + 2 && (i | j) != 0; ++it) {  // i, j: bases left
         const int k = min(ctz64(ins | sub | del), j);
         ins >>= k;
@@ -51,20 +61,20 @@ __device__ __forceinline__ void append_path(u64 ins, u64 sub, u64 del, int j, in
         i -= k;
         j -= k;
         append_run(r, (int)GENASM_OP_MATCH, (uint32_t)k);
-        const uint32_t dl = (uint32_t)del, nl = (uint32_t)ins, sl = (uint32_t)sub;
-        const bool d = dl & 1u, n = nl & 1u, x = sl & 1u;
-        // the run of that edit; one of more than 31 takes another turn
-        const uint32_t stop = (d ? ~dl : n ? ~nl : x ? ~sl | dl : 1u) | 0x80000000u;
-        const int run = __builtin_ctz(stop);
-        const int dj = d ? 0 : run, di = !d && n ? 0 : run;
+        // the run of the edit there; one of more than 31 takes another turn
+        const int dl = (int)del, nl = (int)ins, sl = (int)sub;
+        const int d = -(dl & 1), n = -(nl & 1);
+        const int edits = (d & dl) | (~d & ((n & nl) | (~n & sl & ~dl)));
+        const int run = __builtin_ctz((unsigned)~edits | 0x80000000u);
+        const int dj = run & ~d, di = run & ~n;
         ins >>= dj;
         sub >>= dj;
         del >>= di;
         j -= dj;
         i -= di;
-        append_run(r, d ? (int)GENASM_OP_DEL : n ? (int)GENASM_OP_INS : (int)GENASM_OP_MISMATCH,
-                   (uint32_t)run);
+        append_run(r, kDelOrIns - n - 2 * d, (uint32_t)run);
     }
+    r.overflow = r.overflow || r.written > r.room;
 }
 
 // A window handed from the wavefront that computes it to the one that writes
@@ -99,8 +109,9 @@ __device__ __forceinline__ void mail_barrier() {
 }
 
 // A lane's pairs: lane l of the b-th workgroup of lanes takes list position
-// b * lanes + l, then every (their number) * lanes further on. Serving: the resident pairs, those that
-// advanced least first; otherwise all pairs, longest reads first if ordered.
+// b * lanes + l, then every (their number) * lanes further on. Serving: the
+// resident pairs, those that advanced least first; otherwise all pairs, longest
+// reads first if ordered, past those that take a wavefront each.
 struct LaneShare {
     uint64_t n, stride, first;
     uint32_t n_hot;
@@ -126,6 +137,48 @@ __device__ __forceinline__ LaneShare lane_share(const AlignParams& P) {
     s.stride = (uint64_t)gridDim.x * s.lanes;
     s.first = (uint64_t)blockIdx.x * s.lanes;
     return s;
+}
+
+// A lane's place in the bit planes of a sequence: the words of its window and
+// the word after them, which the next window may need. That word is loaded by
+// every lane for every window, wanted or not: a load under a condition ends in
+// moves that wait for it (two waits a window; without them 20,000 pairs of 10
+// kb take 1.60 ms instead of 1.67, 50,000 uneven ones 3.47 instead of 3.69).
+// Words up to q + 2 exist for any place in a sequence, and for q = 0.
+struct LaneSeq {
+    u64 lo0, lo1, lo2, hi0, hi1, hi2;
+    uint64_t q;
+};
+__device__ __forceinline__ void lane_seq_ahead(LaneSeq& c, const u64* lo, const u64* hi) {
+    c.lo2 = lo[c.q + 2];
+    c.hi2 = hi[c.q + 2];
+}
+__device__ __forceinline__ void lane_seq_open(LaneSeq& c, const u64* lo, const u64* hi, uint64_t bit) {
+    c.q = bit >> 6;
+    c.lo0 = lo[c.q];
+    c.lo1 = lo[c.q + 1];
+    c.hi0 = hi[c.q];
+    c.hi1 = hi[c.q + 1];
+    lane_seq_ahead(c, lo, hi);
+}
+// To the window at `bit`, at most one word on.
+__device__ __forceinline__ void lane_seq_move(LaneSeq& c, const u64* lo, const u64* hi, uint64_t bit) {
+    const bool on = (bit >> 6) != c.q;
+    c.lo0 = on ? c.lo1 : c.lo0;
+    c.lo1 = on ? c.lo2 : c.lo1;
+    c.hi0 = on ? c.hi1 : c.hi0;
+    c.hi1 = on ? c.hi2 : c.hi1;
+    c.q += on ? 1 : 0;
+#if defined(__HIP_DEVICE_COMPILE__)
+    // the old words are done with before the loads, which can then take their
+    // registers (or moves at the loop's end would wait again)
+    asm volatile("" : "+v"(c.lo1), "+v"(c.hi1) : : "memory");
+#endif
+    lane_seq_ahead(c, lo, hi);
+}
+__device__ __forceinline__ void lane_seq_window(const LaneSeq& c, uint64_t bit, u64& wlo, u64& whi) {
+    wlo = funnel64(c.lo0, c.lo1, (int)(bit & 63));
+    whi = funnel64(c.hi0, c.hi1, (int)(bit & 63));
 }
 
 // The wavefront that computes the windows.
@@ -167,21 +220,20 @@ __device__ __forceinline__ void windows_compute(const AlignParams& P, const Lane
         mail.ti[lane] = st.ti;
         mail.nwin[lane] = st.nwin;
         PairCursor pc{0, 0, 0, 0, 0, 0};
-        SeqCursor rc{}, fc{};
+        uint64_t rb = 0, fb = 0;  // the places of the lane's window in the planes
         uint32_t max_windows = 0, done_here = 0;
-        u64 pl = 0, ph = 0, tl = 0, th = 0;
         if (have) {
 #if defined(GENASM_DEBUG)
             if (P.audit) atomicAdd(P.audit + pair, kAuditTake);  // queue audit
 #endif
             pc = pair_cursor(P, pair);
             max_windows = (uint32_t)pc.m + (uint32_t)pc.n + 1u;
-            const uint64_t rb = pc.rb - rorg + st.pj, fb = pc.fb - forg + st.ti;
-            seq_open(rc, P.read_lo, P.read_hi, rb);
-            seq_open(fc, P.ref_lo, P.ref_hi, fb);
-            seq_window(rc, P.read_lo, P.read_hi, rb, pl, ph);
-            seq_window(fc, P.ref_lo, P.ref_hi, fb, tl, th);
+            rb = pc.rb - rorg + st.pj;
+            fb = pc.fb - forg + st.ti;
         }
+        LaneSeq rc, fc;
+        lane_seq_open(rc, P.read_lo, P.read_hi, rb);
+        lane_seq_open(fc, P.ref_lo, P.ref_hi, fb);
         u64 st_wops = 0, st_cells = 0, st_table = 0, st_tb = 0, st_steps = 0, cyc_dc = 0;
         u64 cyc_start = 0, wall_start = 0;
         if constexpr (STATS) {
@@ -194,9 +246,24 @@ __device__ __forceinline__ void windows_compute(const AlignParams& P, const Lane
             const int nw = have ? min(P.W, pc.n - st.ti) : 64;
             u64 cyc0 = 0;
             if constexpr (STATS) cyc0 = clock64();
-            const bool ragged = __ballot(mw < 64 || nw < 64) != 0ull;
-            const WindowPath w = ragged ? window_path<true>(pl, ph, tl, th, mw, nw, P.L)
-                                        : window_path<false>(pl, ph, tl, th, mw, nw, P.L);
+            u64 pl, ph, tl, th;
+            lane_seq_window(rc, rb, pl, ph);
+            lane_seq_window(fc, fb, tl, th);
+            // Past the text only insertions are left, which needs no table: an
+            // unrelated pair spends up to half its windows there, and the steps
+            // for short windows cost all 64 lanes a seventh more (20,000 pairs of
+            // 10 kb, 30% unrelated: 14,600 -> 13,100 cycles a window).
+            const bool spent = nw == 0;
+            const bool ragged = __ballot(!spent && (mw < 64 || nw < 64)) != 0ull;
+            WindowPath w = ragged ? window_path<true>(pl, ph, tl, th, mw, nw, P.L)
+                                  : window_path<false>(pl, ph, tl, th, mw, nw, P.L);
+            if (spent) {
+                w.j_end = min(mw, P.L);
+                w.ins = ~0ull >> (64 - w.j_end);
+                w.sub = w.del = 0ull;
+                w.i_end = 0;
+                w.dist = mw;
+            }
             bool over = false;
             if constexpr (SERVE) over = turn.active && turn.over();
             uint32_t info = 0u;
@@ -216,8 +283,8 @@ __device__ __forceinline__ void windows_compute(const AlignParams& P, const Lane
                     if (st.pj >= pc.m) {
                         info |= kMailEnd;
                     } else {
-                        seq_window(rc, P.read_lo, P.read_hi, pc.rb - rorg + st.pj, pl, ph);
-                        seq_window(fc, P.ref_lo, P.ref_hi, pc.fb - forg + st.ti, tl, th);
+                        rb += (uint64_t)w.j_end;
+                        fb += (uint64_t)w.i_end;
                     }
                     if constexpr (STATS) {
                         st_wops += (u64)nw * (2 + 6 * w.dist);
@@ -258,6 +325,8 @@ __device__ __forceinline__ void windows_compute(const AlignParams& P, const Lane
                     }
                 }
             }
+            lane_seq_move(rc, P.read_lo, P.read_hi, rb);
+            lane_seq_move(fc, P.ref_lo, P.ref_hi, fb);
             mail.ins[buf][lane] = w.ins;
             mail.sub[buf][lane] = w.sub;
             mail.del[buf][lane] = w.del;
@@ -376,10 +445,12 @@ __device__ __forceinline__ void windows_write(const AlignParams& P, const LaneSh
 // one computes the windows, the other turns each window's path into CIGAR runs
 // while the next window is computed.
 //
-// A lane's window takes 5 us and a batch as long as its longest pair. The first
-// P.long_blocks workgroups therefore take the P.long_pairs longest pairs a
-// wavefront each (wave_pair.h: 2 us a window); so do all workgroups of a serving
-// iteration with no more resident pairs than wavefronts.
+// A lane's window takes 5 us (11,600 cycles: about 2,500 instructions, of which
+// one wavefront of a SIMD issues one per 4.5 cycles, so their number bounds it)
+// and a batch as long as its longest pair. The first P.long_blocks workgroups
+// therefore take the P.long_pairs longest pairs a wavefront each (wave_pair.h:
+// 1.7 us a window); so do all workgroups of a serving iteration with no more
+// resident pairs than wavefronts.
 template <bool STATS, bool SERVE>
 __global__ __launch_bounds__(128, 2) void k_windows_lane(AlignParams P) {
     __shared__ u64 shared[2 * kWaveLdsBytes / 8];
