@@ -137,8 +137,9 @@ struct AlignParams {
     int32_t route;              // search: append finished pairs to the window lists
     int32_t compact;            // window kernel: compact 16-lane groups (32-bit table slices)
     int32_t pair_lanes;         // one pair per lane: lanes of a wavefront that take a pair
-    int32_t long_pairs;         // there: pairs (the first of `order`) that take a wavefront each,
-    int32_t long_blocks;        // and the workgroups of two wavefronts that run them
+    int32_t turned_from;        // there: the first workgroup whose wavefronts change roles
+    int32_t long_pairs;         // there: at most so many first pairs of `order` take a wavefront
+    int32_t long_bases;         // each, as far as their reads are longer than this
     int32_t search_parts_log;   // one search part per lane: log2 of a pair's parts
     // Optional per-pair layout (serving: sequences sit anywhere in a device pool).
     const uint32_t* read_len;   // if set, pair i's read is [read_off[i], read_off[i] + read_len[i])

@@ -2514,7 +2514,7 @@ hipError_t launch_windows_serve(const AlignParams& p, int blocks, hipStream_t s)
 }
 
 hipError_t launch_windows_lane(const AlignParams& p, uint64_t max_blocks, int* n_blocks, hipStream_t s) {
-    const uint64_t want = p.long_blocks + (p.n_pairs - p.long_pairs + p.pair_lanes - 1) / p.pair_lanes;
+    const uint64_t want = (p.long_pairs + 1) / 2 + (p.n_pairs + p.pair_lanes - 1) / p.pair_lanes;
     const unsigned blocks = (unsigned)(max_blocks && want > max_blocks ? max_blocks : want);
     const dim3 grid(blocks), block(128);
     *n_blocks = (int)blocks;

@@ -111,16 +111,17 @@ __device__ __forceinline__ void mail_barrier() {
 // A lane's pairs: lane l of the b-th workgroup of lanes takes list position
 // b * lanes + l, then every (their number) * lanes further on. Serving: the
 // resident pairs, those that advanced least first; otherwise all pairs, longest
-// reads first if ordered, past those that take a wavefront each.
+// reads first if ordered, from the first that doesn't take a wavefront on.
 struct LaneShare {
     uint64_t n, stride, first;
     uint32_t n_hot;
-    int lanes;
+    int lanes, n_long, long_blocks;
 };
 template <bool SERVE>
-__device__ __forceinline__ LaneShare lane_share(const AlignParams& P) {
+__device__ __forceinline__ LaneShare lane_share(const AlignParams& P, int lane) {
     LaneShare s;
     s.n_hot = 0;
+    s.n_long = s.long_blocks = 0;
     if constexpr (SERVE) {
         s.n_hot = __hip_atomic_load(P.counters + kCounterEasyLen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         s.n = s.n_hot + (uint64_t)__hip_atomic_load(P.counters + kCounterHardLen, __ATOMIC_RELAXED,
@@ -130,8 +131,10 @@ __device__ __forceinline__ LaneShare lane_share(const AlignParams& P) {
     } else {
         s.n = P.n_pairs;
         s.lanes = P.pair_lanes;
-        s.stride = (uint64_t)((int)gridDim.x - P.long_blocks) * s.lanes;
-        s.first = (uint64_t)P.long_pairs + (uint64_t)((int)blockIdx.x - P.long_blocks) * s.lanes;
+        s.n_long = long_count(P, lane);
+        s.long_blocks = (s.n_long + 1) / 2;
+        s.stride = (uint64_t)((int)gridDim.x - s.long_blocks) * s.lanes;
+        s.first = (uint64_t)s.n_long + (uint64_t)((int)blockIdx.x - s.long_blocks) * s.lanes;
         return s;
     }
     s.stride = (uint64_t)gridDim.x * s.lanes;
@@ -447,9 +450,9 @@ __device__ __forceinline__ void windows_write(const AlignParams& P, const LaneSh
 //
 // A lane's window takes 5 us (11,600 cycles: about 2,500 instructions, of which
 // one wavefront of a SIMD issues one per 4.5 cycles, so their number bounds it)
-// and a batch as long as its longest pair. The first P.long_blocks workgroups
-// therefore take the P.long_pairs longest pairs a wavefront each (wave_pair.h:
-// 1.7 us a window); so do all workgroups of a serving iteration with no more
+// and a batch as long as its longest pair. The first workgroups
+// therefore take the longest pairs a wavefront each, if the lengths are uneven
+// (wave_pair.h: 1.7 us a window); so do all workgroups of a serving iteration with no more
 // resident pairs than wavefronts.
 template <bool STATS, bool SERVE>
 __global__ __launch_bounds__(128, 2) void k_windows_lane(AlignParams P) {
@@ -457,19 +460,19 @@ __global__ __launch_bounds__(128, 2) void k_windows_lane(AlignParams P) {
     static_assert(sizeof(LaneMail) <= sizeof(shared), "layout");
     const int lane = threadIdx.x & 63, wave = uniform((int)(threadIdx.x >> 6));
     uint8_t* lev = reinterpret_cast<uint8_t*>(shared) + wave * kWaveLdsBytes;
-    const LaneShare share = lane_share<SERVE>(P);
+    const LaneShare share = lane_share<SERVE>(P, lane);
     if constexpr (SERVE) {
         if (share.n <= 2ull * gridDim.x) {
             windows_few(P, lev, share.n_hot, (uint32_t)share.n, (uint32_t)blockIdx.x + (uint32_t)wave * gridDim.x,
                         2u * gridDim.x, lane);
             return;
         }
-    } else if ((int)blockIdx.x < P.long_blocks) {
-        windows_long<STATS>(P, lev, (uint64_t)blockIdx.x * 2 + wave, lane);
+    } else if ((int)blockIdx.x < share.long_blocks) {
+        windows_long<STATS>(P, lev, (int)blockIdx.x * 2 + wave, share.n_long, lane);
         return;
     }
     LaneMail& mail = *reinterpret_cast<LaneMail*>(shared);
-    if (wave == 0) windows_compute<STATS, SERVE>(P, share, mail, lane);
+    if (wave == ((int)blockIdx.x >= P.turned_from ? 1 : 0)) windows_compute<STATS, SERVE>(P, share, mail, lane);
     else windows_write<STATS, SERVE>(P, share, mail, lane);
 }
 

@@ -434,15 +434,25 @@ int align_lanes(genasm_ctx* ctx, AlignParams p, const genasm_launch& L, uint64_t
     // a wavefront, 2.9 ms 32 to a wavefront.
     p.pair_lanes = 1;
     while (p.pair_lanes < 64 && (uint64_t)ctx->num_cus * 2 * p.pair_lanes < p.n_pairs) p.pair_lanes *= 2;
+    // A compute unit's next workgroup starts on the SIMD of the last one's second
+    // wavefront. Where two are the most on a unit, the second changes its roles, so
+    // that no computing wavefront shares a SIMD while another SIMD is idle (30,000
+    // pairs of 10 kb: windows 1.62 -> 1.40 ms). With three that puts two computing
+    // ones on a SIMD (40,000: 2.23 -> 2.43), with four there is one of each on
+    // every SIMD as it is.
+    const uint64_t lane_blocks = (p.n_pairs + p.pair_lanes - 1) / p.pair_lanes;
+    p.turned_from = lane_blocks <= (uint64_t)ctx->num_cus * 2 ? ctx->num_cus : INT32_MAX;
     const uint64_t max_blocks = (uint64_t)ctx->num_cus * L.workers_per_cu;
     if (L.lpt_order && max_blocks == 0) {
-        // A batch ends with its longest chains of windows, and a wavefront of its
-        // own runs a chain of related bases in 1.7 us a window, a lane in 5: the
-        // longest pairs, at most one per compute unit, start on those (50,000
-        // uneven pairs: windows 4.87 -> 4.35 ms; twice as many gain nothing there
-        // and cost 20,000 pairs of 10 kb 1.82 -> 2.21 ms).
-        p.long_pairs = (int)std::min<uint64_t>(p.n_pairs / 16, (uint64_t)ctx->num_cus);
-        p.long_blocks = (p.long_pairs + 1) / 2;
+        // A batch of uneven lengths ends with its longest chains of windows, and a
+        // wavefront of its own runs a chain of related bases in 1.7 us a window, a
+        // lane in 5: the longest pairs start on those (50,000 of 100 b to 30 kb:
+        // windows 3.99 ms without, 3.48 with 256 of them, 3.37 with 384, as with
+        // 1,024). Where the lengths are alike they only take SIMDs from the lanes
+        // (20,000 of 10 kb: 1.37 ms without, 1.61 with 128), so only reads of more
+        // than twice the mean are taken.
+        p.long_pairs = (int)std::min<uint64_t>(p.n_pairs / 16, (uint64_t)ctx->num_cus * 3 / 2);
+        p.long_bases = (int)std::min<uint64_t>(2 * (total_read_bases / p.n_pairs), INT32_MAX);
     }
     CHECK_HIP(ctx, mark(0));
     CHECK_HIP(ctx, launch_lane_prep(p, total_read_bases, total_ref_bases, s));

@@ -589,11 +589,22 @@ __global__ __launch_bounds__(64) void k_pair_wave(AlignParams P) {
     wave_pair_windows<STATS, false>(P, pair, pc, col, fresh_state(col), reinterpret_cast<uint8_t*>(smem), lane, none);
 }
 
+// How many first pairs of the order take a wavefront each in the window kernel,
+// looked for at 64 places at once (the order is by classes of length, so that
+// neighbours may be out of order; all wavefronts get the same number).
+__device__ __forceinline__ int long_count(const AlignParams& P, int lane) {
+    if (P.long_pairs == 0) return 0;
+    const int step = (P.long_pairs + 63) / 64, at = lane * step;
+    const bool is = at < P.long_pairs && pair_cursor(P, P.order[at]).m > P.long_bases;
+    const u64 other = ~__ballot(is);
+    return min(other ? __builtin_ctzll(other) * step : P.long_pairs, P.long_pairs);
+}
+
 // The window kernel's wavefronts that take a pair each (see k_windows_lane): one
 // of the longest pairs of a batch, or (serving) a share of the resident pairs.
 template <bool STATS>
-__device__ __forceinline__ void windows_long(const AlignParams& P, uint8_t* lev, uint64_t at, int lane) {
-    if (at >= (uint64_t)P.long_pairs) return;
+__device__ __forceinline__ void windows_long(const AlignParams& P, uint8_t* lev, int at, int n_long, int lane) {
+    if (at >= n_long) return;
     const uint64_t pair = P.order[at];
     if (search_outcome(P, pair) < 0) return;  // the same in every lane
 #if defined(GENASM_DEBUG)
