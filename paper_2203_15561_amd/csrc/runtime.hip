@@ -382,20 +382,23 @@ bool default_geometry(const genasm_launch& L) {
 }
 
 // Whether such a launch takes one pair per wavefront, the plain form's kernel:
-// up to eight wavefronts per CU. Its windows cost a quarter to half of a lane's
-// (wave_pair.h) as long as the wavefronts have a SIMD to themselves and there is
-// one launch instead of seven: 4 reads of 150 bases take 20 us against 50, 1,000
-// of 100 24 against 47, 67 of 30 kb 1.5 ms against 3.9, 2,000 of 3 kb 451 us
-// against 489 (with 30% decoys 595 against 561), 8,000 of 3 kb 850 against 557.
-// Its start search has 64 parts whatever the reference, so much longer
-// references than reads go to the other path.
+// up to eight wavefronts per CU. Its windows cost a third to nearly all of a
+// lane's (wave_pair.h) as long as few wavefronts share a SIMD, and there is one
+// launch instead of seven: 4 reads of 150 bases take 15 us against 50, 1,000 of
+// 100 16 against 47, 67 of 30 kb 1.3 ms against 3.9, 2,000 of 3 kb 350 us against
+// 450 (with 30% unrelated pairs 454 against 450), 4,000 of 3 kb 457 against 449
+// (684 against 456). Short reads, whose seven launches take longer than their
+// windows, go there up to twice as many: 4,000 of 250 44 us against 78, 8,000 of
+// 100 78 against 65. Its start search has 64 parts whatever the reference, so
+// much longer references than reads go to the other path.
 bool wave_path(const genasm_ctx* ctx, uint64_t n_pairs, uint64_t total_ref_bases) {
-    return n_pairs <= (uint64_t)ctx->num_cus * 8 && total_ref_bases / n_pairs <= 65536;
+    const uint64_t mean = total_ref_bases / n_pairs;
+    return n_pairs <= (uint64_t)ctx->num_cus * (mean <= 512 ? 16 : 8) && mean <= 65536;
 }
 
 // Whether it takes one pair per lane (lanes.h) otherwise: when its windows commit
 // no more bases than that path keeps columns for. At 20,000 pairs of 10 kb the
-// start search and the windows take 0.25 and 1.8 ms on it, 2.7 and 15.6 ms on the
+// start search and the windows take 0.25 and 1.4 ms on it, 2.7 and 15.6 ms on the
 // row tables.
 bool lane_path(int commit) { return commit <= kLanePathCommit; }
 
@@ -430,8 +433,8 @@ int align_lanes(genasm_ctx* ctx, AlignParams p, const genasm_launch& L, uint64_t
         ++p.search_parts_log;
     // Pairs per wavefront: as few as leave every SIMD one wavefront (a workgroup
     // has two). A SIMD with one wavefront already issues at nine tenths of its
-    // rate, so sharing SIMDs costs time: 20,000 pairs of 10 kb take 1.8 ms 64 to
-    // a wavefront, 2.9 ms 32 to a wavefront.
+    // rate, so sharing SIMDs costs time: 20,000 pairs of 10 kb took 1.8 ms 64 to
+    // a wavefront and 2.9 ms 32 to a wavefront.
     p.pair_lanes = 1;
     while (p.pair_lanes < 64 && (uint64_t)ctx->num_cus * 2 * p.pair_lanes < p.n_pairs) p.pair_lanes *= 2;
     // A compute unit's next workgroup starts on the SIMD of the last one's second

@@ -69,16 +69,19 @@ def test_wavefront_kernel_emulated(tmp_path):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,form", [(1, None), (65, None), (2047, None), (2048, ga.FORM_PLAIN),
-                                    (2049, None), (4097, None), (33_001, None)])
+                                    (2049, None), (4096, None), (4097, None), (33_001, None)])
 @pytest.mark.parametrize("W,O,k", [(64, 24, 64), (64, 24, 9), (64, 32, 64), (64, 23, 64), (33, 9, 64),
                                    (40, 0, 40), (8, 7, 3)])
 def test_batched_launch_at_its_edges(n, form, W, O, k):
-    # up to 2,048 pairs one per wavefront, past that 8, 16 and 64 pairs per
-    # wavefront and a last one that is not full; reads and references around 0, 1,
+    # up to 4,096 short pairs (2,048 where one reference makes them long on
+    # average) one per wavefront, past that 8, 16 and 64 pairs per wavefront and
+    # a last one that is not full; reads and references around 0, 1,
     # 40, 64 and 128 bases and around several search parts, unrelated pairs (deep
     # windows); W - O of 40 and less (the lane path) and of 41 (the row tables)
     reads, refs = pairs_of(n, 900 + W + O, [150, 0, 1, 39, 40, 41, 63, 64, 65, 104, 129, 600],
                            [170, 64, 0, 1, 63, 65, 128, 129, 640, 1500])
+    if n == 2049:
+        refs[5] = gen.random_bases(gen.pair_rng(901, n), 600 * n)
     ps = gen.from_lists("edges", reads, refs, k, W, O)
     want_all = expected_of(ps)
     with ga.Context(0) as ctx:
