@@ -469,7 +469,7 @@ def main():
         "gcups": cells / (ms_step / 1e3) / 1e9,
         "window_kernel_ms": float(np.mean(win_ms)),
         "search_ms": float(np.mean(search_ms)),
-        "roofline": {"bound": "alu", "kernel": "k_windows (window DC + traceback)",
+        "roofline": {"bound": "alu", "kernel": "k_windows_lane (window DC + traceback)",
                      "achieved": achieved, "peak": INT32_PEAK_TOPS, "unit": "TOP/s",
                      "frac": achieved / INT32_PEAK_TOPS, "traffic": None,
                      "ops_per_launch": int_ops_windows,
