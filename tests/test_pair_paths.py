@@ -94,6 +94,33 @@ def test_batched_launch_at_its_edges(n, form, W, O, k):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("shift", [0, 1, 4, 8, 13])
+def test_packed_streams_at_any_address(shift):
+    # the planes come from 8-byte loads of aligned streams and bytes otherwise, up
+    # to the stream's last byte: the host form's results at every alignment
+    import torch
+
+    def stream(seqs):
+        codes = np.concatenate(seqs)
+        codes = np.concatenate([codes, np.zeros(-len(codes) % 4, np.uint8)]).reshape(-1, 4)
+        packed = (codes << np.array([0, 2, 4, 6], np.uint8)).sum(axis=1).astype(np.uint8)
+        t = torch.full((shift + len(packed),), 255, dtype=torch.uint8, device="cuda")
+        t[shift:] = torch.from_numpy(packed).cuda()
+        off = np.concatenate([[0], np.cumsum([len(q) for q in seqs])])
+        return t[shift:], torch.from_numpy(off.astype(np.int64)).cuda()
+
+    reads, refs = pairs_of(4100, 77, [70, 41, 64, 133], [90, 64, 150])
+    with ga.Context(0) as ctx:
+        want, _ = ctx.align(reads, refs, 64)
+        (r, ro), (f, fo) = stream(reads), stream(refs)
+        out, _ = ctx.align_dev(r, ro, f, fo, 64)
+        torch.cuda.synchronize()
+    got = out.cpu().numpy().reshape(-1).view(ga.RESULT_DTYPE)
+    for field in ("edit_distance", "ref_begin", "ref_end", "n_windows", "flags"):
+        assert (got[field] == want[field]).all(), field
+
+
+@pytest.mark.gpu
 def test_one_read_against_a_long_reference():
     # more search parts than lanes of a wavefront: the parts' keys combine in
     # device memory
