@@ -20,6 +20,7 @@
 #include <cstring>
 #include <memory>
 #include <thread>
+#include <type_traits>
 #include <vector>
 
 #define __global__
@@ -47,10 +48,12 @@ inline hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, K, int, s
     return hipSuccess;
 }
 
+// By value: with A and B alike, the type of (a < b ? a : b) is a reference to a parameter.
 template <class A, class B>
-inline auto min(A a, B b) -> decltype(a < b ? a : b) { return a < b ? a : b; }
+inline std::common_type_t<A, B> min(A a, B b) { return a < b ? a : b; }
 template <class A, class B>
-inline auto max(A a, B b) -> decltype(a < b ? a : b) { return a < b ? b : a; }
+inline std::common_type_t<A, B> max(A a, B b) { return a < b ? b : a; }
+static_assert(!std::is_reference_v<decltype(min(1, 2))> && !std::is_reference_v<decltype(max(1, 2))>);
 
 namespace emu {
 
