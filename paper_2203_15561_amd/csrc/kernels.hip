@@ -2517,7 +2517,7 @@ hipError_t launch_search_lane_items(const AlignParams& p, int blocks, hipStream_
 }
 
 hipError_t launch_windows_serve(const AlignParams& p, int blocks, hipStream_t s) {
-    hipLaunchKernelGGL((k_windows_lane<false, true>), dim3(blocks), dim3(128), 0, s, p);
+    hipLaunchKernelGGL((k_windows_lane<false, true>), dim3(blocks), dim3(128), kLaneLdsBytes, s, p);
     return hipGetLastError();
 }
 
@@ -2526,8 +2526,8 @@ hipError_t launch_windows_lane(const AlignParams& p, uint64_t max_blocks, int* n
     const unsigned blocks = (unsigned)(max_blocks && want > max_blocks ? max_blocks : want);
     const dim3 grid(blocks), block(128);
     *n_blocks = (int)blocks;
-    if (p.stats) hipLaunchKernelGGL((k_windows_lane<true, false>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((k_windows_lane<false, false>), grid, block, 0, s, p);
+    if (p.stats) hipLaunchKernelGGL((k_windows_lane<true, false>), grid, block, kLaneLdsBytes, s, p);
+    else hipLaunchKernelGGL((k_windows_lane<false, false>), grid, block, kLaneLdsBytes, s, p);
     return hipGetLastError();
 }
 

@@ -85,14 +85,19 @@ constexpr uint32_t kMailInternal = 1u << 18;  // it committed nothing (never exp
 constexpr uint32_t kMailEnd = 1u << 19;       // the pair's last window
 constexpr uint32_t kMailPark = 1u << 20;      // serving: the pair's turn ends
 constexpr uint32_t kMailHot = 1u << 21;       // serving: it advanced one window only
+// Everything is kept twice, a window's fields by the parity of the window and a
+// pair's by that of its round of pairs: the writer reads a copy before it comes to
+// its next barrier, so a copy may be filled again once another barrier has passed.
+// A round can be one window long, with one barrier in all, and the next round's
+// fields are filled before there is another.
 struct LaneMail {
     u64 ins[2][64], sub[2][64], del[2][64];
     uint32_t info[2][64];
-    int32_t col[64];     // the pair's start column, -1: no window work
-    uint32_t pair[64];
-    int32_t ti[64];      // its text cursor and window count when the launch took it up
-    uint32_t nwin[64];
     uint32_t more[2];
+    int32_t col[2][64];   // the pair's start column, -1: no window work
+    uint32_t pair[2][64];
+    int32_t ti[2][64];    // its text cursor and window count when the launch took it up
+    uint32_t nwin[2][64];
 };
 
 // Workgroup barrier for what is handed over in LDS. The wavefronts share nothing
@@ -192,8 +197,8 @@ __device__ __forceinline__ void windows_compute(const AlignParams& P, const Lane
     const uint64_t forg = P.planes_from_off0 ? (P.ref_off[0] & ~63ull) : 0;
     TurnClock turn;
     if constexpr (SERVE) turn.open(P);
-    int buf = 0;
-    for (uint64_t first = share.first; first < share.n; first += share.stride) {
+    int buf = 0, round = 0;  // parities
+    for (uint64_t first = share.first; first < share.n; first += share.stride, round ^= 1) {
         const uint64_t at = first + lane;
         bool have = lane < share.lanes && at < share.n;
         uint64_t pair = 0;
@@ -218,10 +223,10 @@ __device__ __forceinline__ void windows_compute(const AlignParams& P, const Lane
                 }
             }
         }
-        mail.col[lane] = col;
-        mail.pair[lane] = (uint32_t)pair;
-        mail.ti[lane] = st.ti;
-        mail.nwin[lane] = st.nwin;
+        mail.col[round][lane] = col;
+        mail.pair[round][lane] = (uint32_t)pair;
+        mail.ti[round][lane] = st.ti;
+        mail.nwin[round][lane] = st.nwin;
         PairCursor pc{0, 0, 0, 0, 0, 0};
         uint64_t rb = 0, fb = 0;  // the places of the lane's window in the planes
         uint32_t max_windows = 0, done_here = 0;
@@ -346,8 +351,8 @@ __device__ __forceinline__ void windows_compute(const AlignParams& P, const Lane
 template <bool STATS, bool SERVE>
 __device__ __forceinline__ void windows_write(const AlignParams& P, const LaneShare& share, const LaneMail& mail,
                                               int lane) {
-    int buf = 0;
-    for (uint64_t first = share.first; first < share.n; first += share.stride) {
+    int buf = 0, round = 0;
+    for (uint64_t first = share.first; first < share.n; first += share.stride, round ^= 1) {
         bool more = true, opened = false;
         uint64_t pair = 0, base = 0;
         PairState st = fresh_state(0);
@@ -358,8 +363,8 @@ __device__ __forceinline__ void windows_write(const AlignParams& P, const LaneSh
             mail_barrier();
             if (!opened) {
                 opened = true;
-                col = mail.col[lane];
-                pair = mail.pair[lane];
+                col = mail.col[round][lane];
+                pair = mail.pair[round][lane];
                 if (col >= 0) {
                     const PairCursor pc = pair_cursor(P, pair);
                     base = pair_run_base(P, pair);
@@ -376,8 +381,8 @@ __device__ __forceinline__ void windows_write(const AlignParams& P, const LaneSh
                             st.flags = ps->flags;
                         }
                     }
-                    st.ti = mail.ti[lane];
-                    st.nwin = mail.nwin[lane];
+                    st.ti = mail.ti[round][lane];
+                    st.nwin = mail.nwin[round][lane];
                     run = RunOut{st.cur_op, st.cur_len, st.written,
                                  (uint32_t)(limit > base ? limit - base : 0ull), P.cigar + base,
                                  (st.flags & kStateOverflow) != 0};
@@ -444,6 +449,9 @@ __device__ __forceinline__ void windows_write(const AlignParams& P, const LaneSh
     }
 }
 
+// A workgroup's LDS: the mail, or the levels of its two wavefronts.
+constexpr int kLaneLdsBytes = 2 * kWaveLdsBytes;
+
 // Window kernel, two wavefronts per workgroup and one pair per lane of them:
 // one computes the windows, the other turns each window's path into CIGAR runs
 // while the next window is computed.
@@ -456,10 +464,10 @@ __device__ __forceinline__ void windows_write(const AlignParams& P, const LaneSh
 // resident pairs than wavefronts.
 template <bool STATS, bool SERVE>
 __global__ __launch_bounds__(128, 2) void k_windows_lane(AlignParams P) {
-    __shared__ u64 shared[2 * kWaveLdsBytes / 8];
-    static_assert(sizeof(LaneMail) <= sizeof(shared), "layout");
+    extern __shared__ u64 smem[];
+    static_assert(sizeof(LaneMail) <= kLaneLdsBytes, "layout");
     const int lane = threadIdx.x & 63, wave = uniform((int)(threadIdx.x >> 6));
-    uint8_t* lev = reinterpret_cast<uint8_t*>(shared) + wave * kWaveLdsBytes;
+    uint8_t* lev = reinterpret_cast<uint8_t*>(smem) + wave * kWaveLdsBytes;
     const LaneShare share = lane_share<SERVE>(P, lane);
     if constexpr (SERVE) {
         if (share.n <= 2ull * gridDim.x) {
@@ -471,7 +479,7 @@ __global__ __launch_bounds__(128, 2) void k_windows_lane(AlignParams P) {
         windows_long<STATS>(P, lev, (int)blockIdx.x * 2 + wave, share.n_long, lane);
         return;
     }
-    LaneMail& mail = *reinterpret_cast<LaneMail*>(shared);
+    LaneMail& mail = *reinterpret_cast<LaneMail*>(smem);
     if (wave == ((int)blockIdx.x >= P.turned_from ? 1 : 0)) windows_compute<STATS, SERVE>(P, share, mail, lane);
     else windows_write<STATS, SERVE>(P, share, mail, lane);
 }

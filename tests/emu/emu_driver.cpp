@@ -3,10 +3,14 @@
 // the device side of the serving loop).
 //
 //   emu_driver IN OUT
-// IN : int64 form (0 plain, 1 batched, 2 serving loop, 3 unimproved, 4 filter), group_lanes, search_lanes,
+// IN : int64 form (0 plain, 1 batched, 2 serving loop, 3 unimproved, 4 filter, 5 batched with
+//      one pair per lane, 6 serving loop with one pair per lane), group_lanes, search_lanes,
 //      lds_rows, k, W, O, n_pairs, read_bytes, ref_bytes, hard_row, window_budget,
 //      slots, admit_per_iteration, hard_lanes, search_chunk, tb_prefetch, hard_share,
-//      serving window time in emulated clock reads (0 = none), compact window groups (0/1);
+//      serving window time in emulated clock reads (0 = none), compact window groups (0/1),
+//      pairs a wavefront (5), window workgroups (5: 0 = as many as the pairs take; 6),
+//      the first workgroup with turned roles (5, 6), long_pairs and long_bases (5),
+//      log2 of a pair's search parts (5);
 //      then
 //      the packed read bytes, the packed reference bytes, read_off[n+1], ref_off[n+1] (uint64).
 // OUT: n genasm_result records, then (read bases + ref bases) CIGAR elements;
@@ -28,7 +32,7 @@ int main(int argc, char** argv) {
     if (argc != 3) { fprintf(stderr, "usage: emu_driver IN OUT\n"); return 2; }
     FILE* f = fopen(argv[1], "rb");
     if (!f) { perror("open IN"); return 2; }
-    int64_t h[20];
+    int64_t h[26];
     if (!read_all(f, h, sizeof h)) return 2;
     const int form = (int)h[0], G = (int)h[1], SG = (int)h[2], lds_rows = (int)h[3];
     const int k = (int)h[4], W = (int)h[5], O = (int)h[6];
@@ -41,6 +45,8 @@ int main(int argc, char** argv) {
     const int hard_share = (int)h[17];
     const uint32_t ticks = (uint32_t)h[18];
     const int compact = (int)h[19];
+    const int pair_lanes = (int)h[20], window_blocks = (int)h[21], turned_from = (int)h[22];
+    const int long_pairs = (int)h[23], long_bases = (int)h[24], parts_log = (int)h[25];
     std::vector<uint8_t> reads(nrb + 8), refs(nfb + 8);
     std::vector<uint64_t> roff(n + 1), foff(n + 1);
     if (!read_all(f, reads.data(), nrb) || !read_all(f, refs.data(), nfb) ||
@@ -72,11 +78,11 @@ int main(int argc, char** argv) {
     // debug build: per-pair audit words, handed to the results by the audit
     // kernel after the window work (plain and batched forms)
     std::vector<uint32_t> audit(std::max<uint64_t>(n, 1), 0u);
-    p.audit = form == 2 ? nullptr : audit.data();
+    p.audit = form == 2 || form == 6 ? nullptr : audit.data();
 #endif
     // bit planes of both streams: from base 0 for the serving loop (slot offsets
     // are absolute), from the first offset otherwise, as the runtime does
-    const bool serve = form == 2;
+    const bool serve = form == 2 || form == 6;
     const uint64_t rbases = serve ? roff[n] : roff[n] - roff[0];
     const uint64_t fbases = serve ? foff[n] : foff[n] - foff[0];
     std::vector<unsigned long long> rlo(plane_words(rbases)), rhi(plane_words(rbases));
@@ -107,14 +113,15 @@ int main(int argc, char** argv) {
         fclose(g);
         return 0;
     }
-    if (form == 2) {
+    if (serve) {
         // Serving loop, device side: slots are reused; each iteration admits
         // up to per_iter pairs into free slots (begin kernel), searches them,
         // then runs the window kernel over the two device lists until the
         // iteration's deadline (`ticks` reads of the emulated clock; 0 = none)
         // or `budget` windows per pair; the kernels move every pair to the
         // next iteration's lists or to the finished list.
-        const int blocks = 2;
+        const bool lanes = form == 6;
+        const int blocks = lanes && window_blocks ? window_blocks : 2;
         const uint64_t workers = (uint64_t)blocks * 4;
         const int spill_rows = 64 - lds_rows;
         std::vector<SearchOut> search(n_slots, SearchOut{kSearchPending, 0});
@@ -160,6 +167,7 @@ int main(int argc, char** argv) {
         p.window_budget = budget;
         p.search_key = key.data();
         p.search_chunk = chunk;
+        p.turned_from = turned_from;
         p.fin_list = fin.data();
         p.fin_len = fin_len.data();
         uint64_t next = 0, finished_n = 0, iters = 0, resident = 0;
@@ -195,19 +203,23 @@ int main(int argc, char** argv) {
             S.list_in = new_list.data();
             S.items_out = items.data();
             launch_search_items(S, n_slots, nullptr);
-            emu::group_lanes = 16;
             S.list_slot = 0;
             S.items_in = items.data();
-            S.items_out = items.data() + icap;
-            launch_search(S, 16, 1, blocks, nullptr);
-            S.items_in = items.data() + icap;
-            S.items_out = items.data();
-            S.list_slot = 1;
-            launch_search(S, 16, 2, blocks, nullptr);
-            S.items_in = items.data();
-            S.items_out = items.data() + icap;
-            S.list_slot = 2;
-            launch_search(S, 16, 4, blocks, nullptr);
+            if (lanes) {
+                launch_search_lane_items(S, blocks, nullptr);
+            } else {
+                emu::group_lanes = 16;
+                S.items_out = items.data() + icap;
+                launch_search(S, 16, 1, blocks, nullptr);
+                S.items_in = items.data() + icap;
+                S.items_out = items.data();
+                S.list_slot = 1;
+                launch_search(S, 16, 2, blocks, nullptr);
+                S.items_in = items.data();
+                S.items_out = items.data() + icap;
+                S.list_slot = 2;
+                launch_search(S, 16, 4, blocks, nullptr);
+            }
             emu::group_lanes = 64;
             launch_search_finalize(S, n_slots, nullptr);
             for (uint32_t i = 0; i < n_new; ++i) {
@@ -227,8 +239,9 @@ int main(int argc, char** argv) {
             P.next_hot = hot[1 - q].data();
             P.next_cold = cold[1 - q].data();
             P.next_len = cnt[1 - q].data();
-            emu::group_lanes = 16;
-            launch_windows(P, blocks, nullptr);
+            emu::group_lanes = lanes ? 64 : 16;
+            if (lanes) launch_windows_serve(P, blocks, nullptr);
+            else launch_windows(P, blocks, nullptr);
             // the finished pairs' results (their CIGARs are already in place)
             for (uint32_t k = 0; k < fin_len[0]; ++k) {
                 const uint32_t sl = fin[k];
@@ -264,6 +277,30 @@ int main(int argc, char** argv) {
         p.lds_rows = 64;
         launch_plain(p, nullptr);
         launch_audit(p, 0, nullptr);  // debug builds only
+    } else if (form == 5) {
+        // the lane path's launches, longest reads first
+        emu::group_lanes = 64;
+        std::vector<SearchOut> search(n, SearchOut{kSearchPending, 0});
+        std::vector<unsigned long long> key(n);
+        std::vector<uint32_t> order(n);
+        std::iota(order.begin(), order.end(), 0u);
+        std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) {
+            return roff[a + 1] - roff[a] > roff[b + 1] - roff[b];
+        });
+        p.search = search.data();
+        p.search_key = key.data();
+        p.order = order.data();
+        p.pair_lanes = pair_lanes;
+        p.turned_from = turned_from;
+        p.long_pairs = long_pairs;
+        p.long_bases = long_bases;
+        p.search_parts_log = parts_log;
+        launch_lane_prep(p, rbases, fbases, nullptr);
+        launch_search_lane(p, nullptr);
+        int used = 0;
+        launch_windows_lane(p, (uint64_t)window_blocks, &used, nullptr);
+        launch_audit(p, 1, nullptr);  // debug builds only
+        fprintf(stderr, "emu: %d window workgroups\n", used);
     } else if (form == GENASM_FORM_UNIMPROVED) {
         emu::group_lanes = 64;
         p.lds_rows = 64;

@@ -61,6 +61,7 @@ struct BlockState {
     int lanes;
     int group_lanes;
     std::vector<std::unique_ptr<std::barrier<>>> bars;
+    std::unique_ptr<std::barrier<>> all;
     unsigned long long slot[256];
     bool pred[256];
 };
@@ -101,7 +102,8 @@ inline int update_dpp(int old, int src, int ctrl, int row_mask, int bank_mask, b
     const int lane = (int)cur.tid;
     b->slot[lane] = (unsigned)src;
     group_barrier();
-    const int from = dpp_source(lane, ctrl);
+    const int wave0 = lane & ~63, source = dpp_source(lane & 63, ctrl);  // within the wavefront
+    const int from = source < 0 ? -1 : wave0 + source;
     int out;
     if (from < 0) out = bound_ctrl ? 0 : old;
     else {
@@ -164,6 +166,7 @@ void launch(K kernel, dim3 grid, dim3 block, size_t lds_bytes, unsigned long lon
         bs.group_lanes = std::min<int>(group_lanes, (int)block.x);
         for (int g = 0; g < bs.lanes / bs.group_lanes; ++g)
             bs.bars.emplace_back(new std::barrier<>(bs.group_lanes));
+        bs.all.reset(new std::barrier<>(bs.lanes));
         std::vector<std::thread> th;
         for (unsigned t = 0; t < block.x; ++t) {
             th.emplace_back([&, t]() {
@@ -249,12 +252,10 @@ inline unsigned alignbit(unsigned hi, unsigned lo, unsigned s) {
 }
 }  // namespace emu
 #define __builtin_amdgcn_alignbit emu::alignbit
-// Block-wide barriers and static shared arrays are not emulated (kernels that
-// use them, such as the ordering scan, do not run under the emulation).
-inline void __syncthreads() {
-    std::fprintf(stderr, "emu: __syncthreads is not emulated\n");
-    std::abort();
-}
+// Reached by all lanes of the block (one that returned before would hang it).
+// Static shared arrays are not emulated: kernels that use them, such as the
+// ordering scan, do not run here.
+inline void __syncthreads() { emu::cur.blk->all->arrive_and_wait(); }
 #define __builtin_amdgcn_s_waitcnt(x) emu::group_barrier()
 #define __builtin_amdgcn_wave_barrier() emu::group_barrier()
 #define __builtin_amdgcn_fence(order, scope) std::atomic_thread_fence(std::memory_order_seq_cst)
