@@ -134,13 +134,16 @@ struct PathWalk {
     uint32_t stay[2];  // columns that didn't move it, the latest in bit 0: 0..31 and 32..39
 };
 
-// bits << 1, and a set bit 0 if x is 0.
+// bits << 1, and a set bit 0 if x is 0; x has at most one bit. Two instructions
+// (its halves' sum less one has its top bit set for 0 only; then a funnel shift)
+// that pass nothing through a condition register: a vector instruction may read one
+// that another wrote only two wait states later.
 __device__ __forceinline__ uint32_t shift_in_zero(uint32_t bits, u64 x) {
+    const uint32_t less_one = (uint32_t)x + (uint32_t)(x >> 32) - 1u;
 #if defined(__HIP_DEVICE_COMPILE__)
-    asm("v_cmp_eq_u64_e32 vcc, 0, %1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(x) : "vcc");
-    return bits;
+    return __builtin_amdgcn_alignbit(bits, less_one, 31);
 #else
-    return (bits << 1) | (x == 0ull ? 1u : 0u);
+    return (bits << 1) | (less_one >> 31);
 #endif
 }
 
