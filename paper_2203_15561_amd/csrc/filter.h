@@ -37,6 +37,18 @@ __device__ __forceinline__ u64 packed_bases(const uint8_t* s, uint64_t nbytes, i
     return sh ? (lo >> sh) | ((u64)w[2] << (64 - sh)) : lo;
 }
 
+// Bit planes of the 64 bases from `base` on.
+__device__ __forceinline__ void packed_planes(const uint8_t* s, uint64_t nbytes, int64_t base, u64& lo, u64& hi) {
+    lo = hi = 0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const u64 w = packed_bases(s, nbytes, base + 32 * h);
+        const uint32_t w0 = (uint32_t)w, w1 = (uint32_t)(w >> 32);
+        lo |= (u64)(even_bits(w0) | (even_bits(w1) << 16)) << (32 * h);
+        hi |= (u64)(even_bits(w0 >> 1) | (even_bits(w1 >> 1) << 16)) << (32 * h);
+    }
+}
+
 // Value of the lane before in the wavefront's row of 16 lanes (lane 0 of the
 // row: 0); `keep` is 0 in the first lane of a group.
 __device__ __forceinline__ uint32_t from_lane_before(uint32_t x, uint32_t keep) {
@@ -113,14 +125,8 @@ __global__ __launch_bounds__(64) void k_filter(const uint8_t* reads, const uint6
     const u64 pad = rows == 64 ? 0ull : ~0ull >> rows;
     u64 a = 0, b = 0;
     if (rows > 0) {
-        u64 lo = 0, hi = 0;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const u64 w = packed_bases(reads, read_bytes, (int64_t)rb + j0 + 32 * h);
-            const uint32_t w0 = (uint32_t)w, w1 = (uint32_t)(w >> 32);
-            lo |= (u64)(even_bits(w0) | (even_bits(w1) << 16)) << (32 * h);
-            hi |= (u64)(even_bits(w0 >> 1) | (even_bits(w1 >> 1) << 16)) << (32 * h);
-        }
+        u64 lo, hi;
+        packed_planes(reads, read_bytes, (int64_t)rb + j0, lo, hi);
         a = __builtin_bitreverse64(lo);
         b = __builtin_bitreverse64(hi);
     }

@@ -24,6 +24,11 @@ struct genasm_ctx {
     // unimproved-form window tables (device)
     char* unimp = nullptr;
     size_t unimp_cap = 0;
+    // one pair per wavefront: where the searchers of a long reference combine
+    // (device); zero between launches, which `tails_clear` says it is
+    char* tails = nullptr;
+    size_t tails_cap = 0;
+    bool tails_clear = false;
     // host-form staging (device)
     char* stage = nullptr;
     size_t stage_cap = 0;
@@ -83,6 +88,12 @@ struct SearchOut {
 constexpr int32_t kSearchFailed = -1;  // no hit within K rows: the result is already written
 constexpr int32_t kSearchDone = -2;    // empty read: the result is already written
 constexpr int32_t kSearchPending = -3; // not searched yet (retry list)
+
+// Where the wavefronts that search one long reference combine (wave_pair.h).
+struct SearchTailSlot {
+    unsigned long long best;   // ~(row << 32 | column) of the least key so far
+    unsigned long long done;   // parts that are in it
+};
 
 // Turn limits of a serving iteration (device wall clock, 100 MHz), written at
 // its start. A resident pair's turn takes at least one window and starts none
@@ -159,6 +170,15 @@ struct AlignParams {
     // Debug builds (GENASM_DEBUG) only: per-pair audit word (kAudit* bits in the
     // low half, the number of workers that took the pair in the high half).
     uint32_t* audit;
+    // Start search of references longer than the columns a pair's own lanes take
+    // (search_own in all; with one pair per lane search_part_cols a part, a multiple
+    // of 64): chunks of 1 << search_tail_log columns, search_own at most, a lane each,
+    // numbered over the whole batch (search_tail in wave_pair.h).
+    uint64_t search_tails;      // lanes for them, 0 = no such reference
+    uint64_t search_own;
+    int32_t search_tail_log;
+    uint32_t search_part_cols;
+    SearchTailSlot* tail_slots; // one pair per wavefront: search_tails of them, zero between launches
 };
 
 // Audit bits of a debug build: an invariant that failed for the pair. The

@@ -2441,9 +2441,15 @@ int search_lds_bytes(int group_lanes) { return (64 / group_lanes) * kSearchGroup
 
 hipError_t launch_plain(const AlignParams& p, hipStream_t s) {
     if (p.n_pairs == 0) return hipSuccess;
-    const dim3 grid((unsigned)p.n_pairs), block(64);
-    if (p.stats) hipLaunchKernelGGL(k_pair_wave<true>, grid, block, kWaveLdsBytes, s, p);
-    else hipLaunchKernelGGL(k_pair_wave<false>, grid, block, kWaveLdsBytes, s, p);
+    const dim3 grid((unsigned)(p.n_pairs + (p.search_tails + 63) / 64)), block(64);
+    if (p.search_tails) {
+        if (p.stats) hipLaunchKernelGGL((k_pair_wave<true, true>), grid, block, kWaveLdsBytes, s, p);
+        else hipLaunchKernelGGL((k_pair_wave<false, true>), grid, block, kWaveLdsBytes, s, p);
+    } else if (p.stats) {
+        hipLaunchKernelGGL((k_pair_wave<true, false>), grid, block, kWaveLdsBytes, s, p);
+    } else {
+        hipLaunchKernelGGL((k_pair_wave<false, false>), grid, block, kWaveLdsBytes, s, p);
+    }
     return hipGetLastError();
 }
 
@@ -2506,8 +2512,8 @@ hipError_t launch_lane_prep(const AlignParams& p, uint64_t n_read, uint64_t n_re
 }
 
 hipError_t launch_search_lane(const AlignParams& p, hipStream_t s) {
-    const uint64_t threads = p.n_pairs << p.search_parts_log;
-    hipLaunchKernelGGL(k_search_lane, dim3((unsigned)((threads + 63) / 64)), dim3(64), 0, s, p);
+    const uint64_t blocks = search_part_blocks(p) + (p.search_tails + 63) / 64;
+    hipLaunchKernelGGL(k_search_lane, dim3((unsigned)blocks), dim3(64), 0, s, p);
     return hipGetLastError();
 }
 

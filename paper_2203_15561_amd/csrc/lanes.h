@@ -572,21 +572,35 @@ __device__ __forceinline__ void search_part(const AlignParams& P, bool have, uin
     if (P.stats) atomicAdd(P.stats + pair * kStatCount + kStatSearchLaneSteps, (u64)(e - c0));
 }
 
+__host__ __device__ __forceinline__ uint64_t search_part_blocks(const AlignParams& P) {
+    return ((P.n_pairs << P.search_parts_log) + 63) / 64;
+}
+
 __global__ __launch_bounds__(64) void k_search_lane(AlignParams P) {
-    const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const uint64_t at = t >> P.search_parts_log;
-    const uint32_t part = (uint32_t)(t & ((1ull << P.search_parts_log) - 1));
-    bool have = at < P.n_pairs;
-    uint64_t pair = 0, cols = 64;
+    uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    bool have;
+    uint64_t pair = 0, cols = 1ull << P.search_tail_log;
+    int64_t c0 = 0;
     PairCursor pc{0, 0, 0, 0, 0, 0};
-    if (have) {
-        pair = P.order ? P.order[at] : at;
-        pc = pair_cursor(P, pair);
-        const uint64_t per = (((uint64_t)pc.n + (1ull << P.search_parts_log) - 1) >> P.search_parts_log);
-        cols = max((uint64_t)64, (per + 63) & ~63ull);
-        have = pc.m > 0 && (uint64_t)part * cols < (uint64_t)pc.n;
+    if (blockIdx.x < search_part_blocks(P)) {
+        const uint64_t at = t >> P.search_parts_log;
+        const uint32_t part = (uint32_t)(t & ((1ull << P.search_parts_log) - 1));
+        have = at < P.n_pairs;
+        if (have) {
+            pair = P.order ? P.order[at] : at;
+            pc = pair_cursor(P, pair);
+            const uint64_t per = (((uint64_t)pc.n + (1ull << P.search_parts_log) - 1) >> P.search_parts_log);
+            cols = min(max((uint64_t)64, (per + 63) & ~63ull), (uint64_t)P.search_part_cols);
+            c0 = (int64_t)(part * cols);
+        }
+    } else {
+        t -= search_part_blocks(P) * 64;
+        uint64_t first;
+        have = t < P.search_tails && search_tail(P, t, pair, c0, first);
+        if (have) pc = pair_cursor(P, pair);
     }
-    search_part(P, have, pair, pc, have ? (int)(part * cols) : 0, cols);
+    have = have && pc.m > 0 && c0 < (int64_t)pc.n;
+    search_part(P, have, pair, pc, have ? (int)c0 : 0, cols);
 }
 
 // Serving: the items of k_search_items (pair << 24 | chunk), one per lane.

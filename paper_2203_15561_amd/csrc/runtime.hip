@@ -281,6 +281,7 @@ void genasm_destroy(genasm_ctx* ctx) {
     if (ctx->scratch) (void)hipFree(ctx->scratch);
     if (ctx->planes) (void)hipFree(ctx->planes);
     if (ctx->unimp) (void)hipFree(ctx->unimp);
+    if (ctx->tails) (void)hipFree(ctx->tails);
     if (ctx->stage) (void)hipFree(ctx->stage);
     if (ctx->dbg) (void)hipFree(ctx->dbg);
     if (ctx->stats) (void)hipFree(ctx->stats);
@@ -381,6 +382,12 @@ bool default_geometry(const genasm_launch& L) {
            L.search_per_cu == 8;
 }
 
+// Columns of a reference that its pair's wavefront searches itself in a batched
+// launch, the rest in chunks on others: 0.13 ms of them (62 ns a column of each of
+// its 64 lanes), and twice the longest mean that goes there, so that references of
+// like lengths are not split.
+constexpr uint32_t kWaveOwnCols = 2048 * 64;
+
 // Whether such a launch takes one pair per wavefront, the plain form's kernel:
 // up to eight wavefronts per CU. Its windows cost a third to nearly all of a
 // lane's (wave_pair.h) as long as few wavefronts share a SIMD, and there is one
@@ -389,8 +396,8 @@ bool default_geometry(const genasm_launch& L) {
 // 450 (with 30% unrelated pairs 454 against 450), 4,000 of 3 kb 457 against 449
 // (684 against 456). Short reads, whose seven launches take longer than their
 // windows, go there up to twice as many: 4,000 of 250 44 us against 78, 8,000 of
-// 100 78 against 65. Its start search has 64 parts whatever the reference, so
-// much longer references than reads go to the other path.
+// 100 78 against 65. Its start search has 64 parts whatever the reference (chunks
+// beyond kWaveOwnCols), so much longer references than reads go to the other path.
 bool wave_path(const genasm_ctx* ctx, uint64_t n_pairs, uint64_t total_ref_bases) {
     const uint64_t mean = total_ref_bases / n_pairs;
     return n_pairs <= (uint64_t)ctx->num_cus * (mean <= 512 ? 16 : 8) && mean <= 65536;
@@ -431,6 +438,18 @@ int align_lanes(genasm_ctx* ctx, AlignParams p, const genasm_launch& L, uint64_t
     const uint64_t mean = total_ref_bases / p.n_pairs;
     while ((p.n_pairs << p.search_parts_log) < 131072 && (mean >> p.search_parts_log) > 512)
         ++p.search_parts_log;
+    // Parts as long as in a reference of twice the mean at most, so that the slowest
+    // lane takes about as long as the others; longer references go on in chunks. Many
+    // short references have larger chunks, since the chunks' lanes look for their
+    // reference whether there are long ones or not (100,000 pairs of 250 bases: 173.9
+    // us with 28,000 such lanes, 172.9 with 7,000; 172.6 without), and long ones small
+    // chunks, of which they have more (50,000 uneven pairs: 3834 us with 4,096
+    // columns, 3672 with 1,024).
+    p.search_tail_log = mean <= 512 && total_ref_bases > 16ull << 20 ? 12 : 10;
+    const uint64_t chunk = 1ull << p.search_tail_log;
+    p.search_part_cols = (uint32_t)std::min<uint64_t>(1u << 30, align_up(std::max(chunk, 2 * mean >> p.search_parts_log), 64));
+    p.search_own = (uint64_t)p.search_part_cols << p.search_parts_log;
+    if (total_ref_bases > p.search_own) p.search_tails = total_ref_bases >> p.search_tail_log;
     // Pairs per wavefront: as few as leave every SIMD one wavefront (a workgroup
     // has two). A SIMD with one wavefront already issues at nine tenths of its
     // rate, so sharing SIMDs costs time: 20,000 pairs of 10 kb took 1.8 ms 64 to
@@ -615,6 +634,34 @@ int align_dev(genasm_ctx* ctx, const uint8_t* d_reads2b, const uint64_t* d_read_
         return GENASM_OK;
     };
     if (L.form == GENASM_FORM_PLAIN) return plain();
+    // The same kernel for a batched launch, where a reference of more than
+    // kWaveOwnCols columns is searched by more wavefronts than its pair's.
+    auto plain_chunked = [&]() -> int {
+        if (total_ref_bases <= kWaveOwnCols) return plain();
+        const uint64_t tails = total_ref_bases >> 10;
+        const size_t bytes = tails * sizeof(SearchTailSlot);
+        if (noalloc) {
+            // the plane area, which this kernel doesn't use (16 times as large)
+            p.tail_slots = reinterpret_cast<SearchTailSlot*>(plane_base);
+            CHECK_HIP(ctx, launch_zero_u32(reinterpret_cast<uint32_t*>(plane_base), bytes / 4, s));
+        } else if (bytes > ctx->tails_cap && ctx->pinned) {
+            return plain();  // captured before a call of this size: without the slots
+        } else {
+            const size_t had = ctx->tails_cap;
+            rc = ensure(ctx, &ctx->tails, &ctx->tails_cap, bytes);
+            if (rc) return rc;
+            if (!ctx->tails_clear || ctx->tails_cap != had) {
+                ctx->tails_clear = false;
+                CHECK_HIP(ctx, launch_zero_u32(reinterpret_cast<uint32_t*>(ctx->tails), ctx->tails_cap / 4, s));
+                ctx->tails_clear = true;
+            }
+            p.tail_slots = reinterpret_cast<SearchTailSlot*>(ctx->tails);
+        }
+        p.search_tails = tails;
+        p.search_tail_log = 10;
+        p.search_own = kWaveOwnCols;
+        return plain();
+    };
 
     // Batched: scratch layout.
     p.lds_rows = L.lds_rows;
@@ -666,7 +713,7 @@ int align_dev(genasm_ctx* ctx, const uint8_t* d_reads2b, const uint64_t* d_read_
     };
     int per_cu = L.workers_per_cu;
     // (the no-allocation call still refuses what the row-table layout would)
-    if (waves && !noalloc) return plain();
+    if (waves && !noalloc) return plain_chunked();
     if (lanes && !noalloc) {
         // no spill, no item lists; the no-allocation call keeps the layout below, so
         // that it takes the same batches as ever
@@ -695,7 +742,7 @@ int align_dev(genasm_ctx* ctx, const uint8_t* d_reads2b, const uint64_t* d_read_
     if (profiling) ctx->prof_window_blocks = win_blocks;
     Carver real{base};
     real.off = base_off;
-    if (waves) return plain();
+    if (waves) return plain_chunked();
     if (lanes) return align_lanes(ctx, p, L, total_read_bases, total_ref_bases, &real, mark, s);
     auto [items, hist, order] = carve(real, workers);
 

@@ -413,13 +413,40 @@ __device__ __forceinline__ int wave_solve(u64 pl, u64 ph, u64 tl, u64 th, int mw
     return d;
 }
 
-// Start search: the wavefront's lanes take parts of the reference; see
-// search_part. A hit within Kr rows reaches at most m1 + Kr columns.
+// Long references. However long the references are on average, one may be as
+// long as the rest together, so a pair's own lanes search no more than its first
+// search_own columns, and the chunks after those get lanes of their own: 2,000 reads of 100 bases, one of them with a reference of 10 Mb, took 9.76
+// ms (100,000 of 250: 488 ms) when its pair's lanes searched all of it, against
+// 0.42 (2.04) by chunks of 4,096 columns on the row tables, and 0.15 (0.26) so.
+//
+// The chunks' lanes need no list. With chunks of C columns, lane x stands at base
+// (x + 1) C of the batch's references; a reference of n columns holds at least
+// floor(n / C) such places, as many as its columns past search_own take as long as
+// C <= search_own. Sets the pair, its first place and the first column of lane x's
+// chunk; false if there is none.
+__device__ __forceinline__ bool search_tail(const AlignParams& P, uint64_t x, uint64_t& pair, int64_t& c0,
+                                            uint64_t& first) {
+    const int log = P.search_tail_log;
+    const uint64_t at = (x + 1) << log, org = P.ref_off[0];
+    uint64_t lo = 0, hi = P.n_pairs - 1;  // the first pair whose reference ends at `at` or later
+    while (lo < hi) {
+        const uint64_t mid = (lo + hi) / 2;
+        if (P.ref_off[mid + 1] - org >= at) hi = mid;
+        else lo = mid + 1;
+    }
+    const uint64_t a = P.ref_off[lo] - org, b = P.ref_off[lo + 1] - org;
+    pair = lo;
+    first = a >> log;
+    const uint64_t c = P.search_own + ((x - first) << log);
+    c0 = (int64_t)c;
+    return at <= b && c < b - a;
+}
+
+// Start search of `cols` output columns from c0 on of a lane's pair; see search_part. A hit within Kr rows reaches at most m1 + Kr columns. All lanes
+// of the wavefront call this together. Returns row << 32 | column.
 __device__ __forceinline__ u64 wave_search(const AlignParams& P, const PairCursor& pc, int m1, int Kr, u64 pl,
-                                           u64 ph, int lane) {
+                                           u64 ph, int64_t c0, int cols) {
     const uint64_t bytes = (P.ref_off[P.n_pairs] + 3) / 4;
-    const int cols = max((pc.n + 63) / 64, 1);
-    const int64_t c0 = (int64_t)lane * cols;
     const int e = (int)min((int64_t)pc.n, c0 + cols + m1 + Kr);
     int nb = c0 < pc.n ? (int)((e - c0 + 31) / 32) : 0;
     const u64 a = __builtin_bitreverse64(pl), b = __builtin_bitreverse64(ph);
@@ -438,8 +465,32 @@ __device__ __forceinline__ u64 wave_search(const AlignParams& P, const PairCurso
         if (k != ~0u) key = min(key, ((u64)(k >> 6) << 32) | (u64)(uint32_t)(col + (int64_t)(k & 63u)));
         --nb;
     }
-    key = wave_min(key, lane);
-    return (int)(key >> 32) <= Kr ? key : ~0ull;
+    return key;
+}
+
+// Adds a wavefront's least key over `parts` parts of a long reference (its pair's
+// own columns, or a chunk a lane) to the others'. True in the wavefront that is
+// the last: `key` is then the least of all, and the slot is as it was. Nothing
+// waits for the others.
+__device__ __forceinline__ bool tail_last(const AlignParams& P, uint64_t first, int n, uint32_t parts, u64& key, int lane) {
+    SearchTailSlot* slot = P.tail_slots + first;
+    const uint32_t all = 2u + (((uint32_t)n - (uint32_t)P.search_own - 1u) >> P.search_tail_log);
+    u64 best = 0;
+    int last = 0;
+    if (lane == 0) {
+        atomicMax(&slot->best, ~key);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        last = atomicAdd(&slot->done, (u64)parts) + parts == all;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        if (last) {
+            best = atomicMax(&slot->best, 0ull);
+            slot->best = 0ull;
+            slot->done = 0ull;
+        }
+    }
+    if (!uniform(last)) return false;
+    key = ~uniform64(best);
+    return true;
 }
 
 // The windows of a pair from the state `st` on, to its end or (serving) to the
@@ -555,26 +606,14 @@ __device__ __forceinline__ PairCursor wave_cursor(const AlignParams& P, uint64_t
     return pc;
 }
 
+// A pair from its search's least key on.
 template <bool STATS>
-__global__ __launch_bounds__(64) void k_pair_wave(AlignParams P) {
-    extern __shared__ u64 smem[];
-    const int lane = threadIdx.x & 63;
-    const uint64_t pair = blockIdx.x;
-    if (pair >= P.n_pairs) return;
-    const PairCursor pc = wave_cursor(P, pair);
-    if (pc.m == 0) {
-        if (lane == 0) finish_without_windows(P, pair, 0);
-        return;
-    }
-    WaveSeq rd;
-    u64 pl, ph;
-    wave_seq_open(rd, P.reads, pc.rb, pc.m, 0, lane);
-    wave_seq_window(rd, 0, lane, pl, ph);
+__device__ __forceinline__ void wave_pair_from_key(const AlignParams& P, uint64_t pair, const PairCursor& pc, u64 key,
+                                                   uint8_t* lev, int lane) {
     const int m1 = min(P.W, pc.m);
     const int Kr = min(P.K, m1 - 1);
-    const u64 key = wave_search(P, pc, m1, Kr, pl, ph, lane);
     int row = -1, col = 0;
-    if (key != ~0ull) {
+    if (key != ~0ull && (int)(key >> 32) <= Kr) {
         row = (int)(key >> 32);
         col = (int)(uint32_t)key;
     } else if (m1 <= P.K) {
@@ -586,7 +625,64 @@ __global__ __launch_bounds__(64) void k_pair_wave(AlignParams P) {
         return;
     }
     TurnClock none;
-    wave_pair_windows<STATS, false>(P, pair, pc, col, fresh_state(col), reinterpret_cast<uint8_t*>(smem), lane, none);
+    wave_pair_windows<STATS, false>(P, pair, pc, col, fresh_state(col), lev, lane, none);
+}
+
+// Workgroup i takes pair i. CHUNKS: the workgroups after the pairs search the
+// chunks of long references, a lane per chunk; the last wavefront to finish a
+// pair's search takes its windows. (An instance of its own, and the windows twice in
+// it: with the chunks' code around them short calls took up to 0.4 us longer.)
+template <bool STATS, bool CHUNKS>
+__global__ __launch_bounds__(64) void k_pair_wave(AlignParams P) {
+    extern __shared__ u64 smem[];
+    uint8_t* lev = reinterpret_cast<uint8_t*>(smem);
+    const int lane = threadIdx.x & 63;
+    const uint64_t pair = blockIdx.x;
+    u64 pl, ph;
+    if (!CHUNKS || pair < P.n_pairs) {
+        if (pair >= P.n_pairs) return;
+        const PairCursor pc = wave_cursor(P, pair);
+        if (pc.m == 0) {
+            if (lane == 0) finish_without_windows(P, pair, 0);
+            return;
+        }
+        WaveSeq rd;
+        wave_seq_open(rd, P.reads, pc.rb, pc.m, 0, lane);
+        wave_seq_window(rd, 0, lane, pl, ph);
+        const bool more = CHUNKS && pc.n > (int)P.search_own;
+        const int m1 = min(P.W, pc.m), cols = max(((more ? (int)P.search_own : pc.n) + 63) / 64, 1);
+        const int64_t c0 = (int64_t)lane * cols;
+        u64 key = wave_min(wave_search(P, pc, m1, min(P.K, m1 - 1), pl, ph, c0, cols), lane);
+        if (CHUNKS && more && !tail_last(P, (P.ref_off[pair] - P.ref_off[0]) >> P.search_tail_log, pc.n, 1u, key, lane)) return;
+        wave_pair_from_key<STATS>(P, pair, pc, key, lev, lane);
+        return;
+    }
+    const uint64_t x = (pair - P.n_pairs) * 64 + (uint64_t)lane;
+    uint64_t of = 0, first = 0;
+    int64_t c0 = 0;
+    PairCursor pc{0, 0, 0, 0, 0, 0};
+    bool have = x < P.search_tails && search_tail(P, x, of, c0, first);
+    pl = ph = 0;
+    if (have) {
+        pc = pair_cursor(P, of);
+        have = pc.m > 0;
+        if (!have) pc.n = 0;  // nothing to search
+        packed_planes(P.reads, (P.read_off[P.n_pairs] + 3) / 4, (int64_t)pc.rb, pl, ph);
+    }
+    u64 todo = __ballot(have);
+    if (todo == 0ull) return;
+    const int m1 = min(P.W, pc.m);
+    const u64 lane_key = wave_search(P, pc, m1, min(P.K, m1 - 1), pl, ph, c0, 1 << P.search_tail_log);
+    while (todo != 0ull) {
+        const int at = __builtin_ctzll(todo);
+        const uint64_t p = (uint32_t)read_lane((int)of, at);
+        const u64 mine = __ballot(have && of == p);
+        todo &= ~mine;
+        u64 key = wave_min(have && of == p ? lane_key : ~0ull, lane);
+        const PairCursor pu = wave_cursor(P, p);
+        if (tail_last(P, read_lane64(first, at), pu.n, (uint32_t)__builtin_popcountll(mine), key, lane))
+            wave_pair_from_key<STATS>(P, p, pu, key, lev, lane);
+    }
 }
 
 // How many first pairs of the order take a wavefront each in the window kernel,

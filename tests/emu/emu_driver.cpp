@@ -10,7 +10,8 @@
 //      serving window time in emulated clock reads (0 = none), compact window groups (0/1),
 //      pairs a wavefront (5), window workgroups (5: 0 = as many as the pairs take; 6),
 //      the first workgroup with turned roles (5, 6), long_pairs and long_bases (5),
-//      log2 of a pair's search parts (5);
+//      log2 of a pair's search parts (5), columns of a part (5) or of a pair's own
+//      wavefront (0), longer references in chunks (0 = no limit);
 //      then
 //      the packed read bytes, the packed reference bytes, read_off[n+1], ref_off[n+1] (uint64).
 // OUT: n genasm_result records, then (read bases + ref bases) CIGAR elements;
@@ -32,7 +33,7 @@ int main(int argc, char** argv) {
     if (argc != 3) { fprintf(stderr, "usage: emu_driver IN OUT\n"); return 2; }
     FILE* f = fopen(argv[1], "rb");
     if (!f) { perror("open IN"); return 2; }
-    int64_t h[26];
+    int64_t h[27];
     if (!read_all(f, h, sizeof h)) return 2;
     const int form = (int)h[0], G = (int)h[1], SG = (int)h[2], lds_rows = (int)h[3];
     const int k = (int)h[4], W = (int)h[5], O = (int)h[6];
@@ -47,6 +48,7 @@ int main(int argc, char** argv) {
     const int compact = (int)h[19];
     const int pair_lanes = (int)h[20], window_blocks = (int)h[21], turned_from = (int)h[22];
     const int long_pairs = (int)h[23], long_bases = (int)h[24], parts_log = (int)h[25];
+    const uint32_t own_cols = (uint32_t)h[26];
     std::vector<uint8_t> reads(nrb + 8), refs(nfb + 8);
     std::vector<uint64_t> roff(n + 1), foff(n + 1);
     if (!read_all(f, reads.data(), nrb) || !read_all(f, refs.data(), nfb) ||
@@ -275,8 +277,16 @@ int main(int argc, char** argv) {
     } else if (form == GENASM_FORM_PLAIN) {
         emu::group_lanes = 64;
         p.lds_rows = 64;
+        p.search_tail_log = 10;
+        std::vector<SearchTailSlot> slots(fbases >> p.search_tail_log);  // exact: ASan sees past it
+        p.search_own = own_cols;
+        p.search_tails = own_cols ? slots.size() : 0;
+        p.tail_slots = slots.data();
         launch_plain(p, nullptr);
         launch_audit(p, 0, nullptr);  // debug builds only
+        for (const SearchTailSlot& t : slots) {
+            if (t.best || t.done) { fprintf(stderr, "a slot of a long reference is left set\n"); return 3; }
+        }
     } else if (form == 5) {
         // the lane path's launches, longest reads first
         emu::group_lanes = 64;
@@ -295,6 +305,10 @@ int main(int argc, char** argv) {
         p.long_pairs = long_pairs;
         p.long_bases = long_bases;
         p.search_parts_log = parts_log;
+        p.search_part_cols = own_cols ? own_cols : 1u << 30;
+        p.search_own = (uint64_t)p.search_part_cols << parts_log;
+        p.search_tail_log = 10;
+        p.search_tails = own_cols ? fbases >> p.search_tail_log : 0;
         launch_lane_prep(p, rbases, fbases, nullptr);
         launch_search_lane(p, nullptr);
         int used = 0;

@@ -278,6 +278,14 @@ inline T atomicMin(T* p, T v) {
     }
     return cur;
 }
+template <class T>
+inline T atomicMax(T* p, T v) {
+    T cur = __atomic_load_n(p, __ATOMIC_SEQ_CST);
+    while (v > cur && !__atomic_compare_exchange_n(p, &cur, v, false, __ATOMIC_SEQ_CST,
+                                                   __ATOMIC_SEQ_CST)) {
+    }
+    return cur;
+}
 
 namespace genasm { extern unsigned long long smem[]; }
 constexpr size_t kEmuLdsWords = 160 * 1024 / 8;

@@ -52,6 +52,97 @@ def test_serving_rounds_emulated(driver, budget, ticks):
     assert got == expected_of(ps)
 
 
+def long_references(n, seed, ref_len, at):
+    """n pairs, every reference of pairs_of but those of `at`: of the given
+    lengths, with the read in their last bases (or nowhere)."""
+    reads, refs = pairs_of(n, seed, [50, 70, 0, 1], [90, 0, 64])
+    for i, m in zip(at, ref_len):
+        refs[i] = gen.random_bases(gen.pair_rng(seed + 1, i), m)
+        reads[i] = gen.random_bases(gen.pair_rng(seed + 2, i), 55)
+        if i % 3:
+            refs[i][-60:-5] = reads[i]
+    return reads, refs
+
+
+@pytest.mark.slow
+def test_long_references_emulated(driver):
+    # references around a pair's own 1,024 columns and the chunks after them, next
+    # to each other and apart, in both paths, and the same without a limit
+    lengths = [1024, 1025, 2048, 2049, 2047, 3100, 4096, 5000]
+    reads, refs = long_references(30, 81, lengths, [0, 4, 5, 6, 13, 20, 28, 29])
+    reads[20] = reads[20][:0]
+    for k in (64, 2):
+        ps = gen.from_lists("long", reads, refs, k)
+        want = expected_of(ps)
+        for own in (1024, 0):
+            assert results(*emu.run(driver, ps, 0, own_cols=own)) == want, (k, own)
+            assert results(*emu.run(driver, ps, emu.LANES, pair_lanes=32, own_cols=own)) == want, (k, own)
+        assert results(*emu.run(driver, ps, emu.LANES, pair_lanes=32, search_parts_log=1, own_cols=512)) == want, k
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [3, 2000, 3000])
+def test_long_references(n):
+    # references of more than 131,072 columns (a wavefront's own) and of many times
+    # the mean (a lane's parts): results, several calls, a captured call, and no
+    # slower than the row tables' search, which cuts all references alike
+    import torch
+
+    lengths = [131_072, 131_073, 400_000, 132_000 if n == 3 else 1_500_000]
+    at = [0, 1, 2] if n == 3 else [1, 2, n // 2, n - 1]
+    reads, refs = long_references(n, 82, lengths[-len(at):], at)
+    ps = gen.from_lists("long", reads, refs, 20)
+    want = expected_of(ps)
+    with ga.Context(0) as ctx:
+        for _ in range(2):
+            assert results(*ctx.align(reads, refs, 20)) == want
+        r, f = torch.from_numpy(emu.pack2b(ps.reads)).cuda(), torch.from_numpy(emu.pack2b(ps.refs)).cuda()
+        ro, fo = (torch.from_numpy(x.astype(np.int64)).cuda() for x in (ps.read_off, ps.ref_off))
+        out, cig = ctx.align_dev(r, ro, f, fo, 20)
+        nr, nf = len(ps.reads), len(ps.refs)
+
+        def call(launch=None):
+            ctx.align_dev(r, ro, f, fo, 20, launch=launch, out=out, cigar=cig, total_read_bases=nr, total_ref_bases=nf)
+
+        def same():
+            got = out.cpu().numpy().reshape(-1).view(ga.RESULT_DTYPE)
+            return all((int(g["edit_distance"]), int(g["ref_begin"]), int(g["ref_end"])) == (w[0], w[2], w[3])
+                       for g, w in zip(got, want))
+
+        def ms(launch):
+            times = []
+            for _ in range(5):
+                a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                a.record()
+                call(launch)
+                b.record()
+                b.synchronize()
+                times.append(a.elapsed_time(b))
+            return min(times)
+
+        assert same()
+        for _ in range(2):
+            out.zero_()
+            ctx.align_dev(r, ro, f, fo, 20, out=out, cigar=cig, total_read_bases=nr, total_ref_bases=nf, noalloc=True)
+            assert same()
+        here, tables = ms(None), ms(ga.make_launch(ga.FORM_BATCHED, search_per_cu=4))
+        assert here < 1.5 * tables, (here, tables)
+        stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            ctx.align_dev(r, ro, f, fo, 20, out=out, cigar=cig, total_read_bases=nr, total_ref_bases=nf,
+                          stream=stream.cuda_stream)
+        for _ in range(3):
+            out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert same()
+            call()
+            torch.cuda.synchronize()
+            assert same()
+        del graph
+        ctx.unpin()
+
+
 @pytest.mark.gpu
 def test_rounds_of_one_window():
     # one workgroup a compute unit: 40,000 pairs are three rounds and more
