@@ -368,8 +368,10 @@ int genasm_validate(const char* reads, uint64_t reads_len, const uint64_t* read_
 typedef struct {
     float total_ms;            /* first to last kernel of the call */
     float order_ms;            /* longest-first ordering (batched form) */
-    float search_ms;           /* start-search kernels (batched form) */
-    float windows_ms;          /* window kernel (batched) or the whole plain kernel */
+    float search_ms;           /* start-search kernels (batched form; about 0 for a batch of few
+                                  pairs, whose search and windows are one kernel) */
+    float windows_ms;          /* window kernel (batched), or the one kernel of the plain form and
+                                  of a batch of few pairs */
     uint64_t n_pairs;
     uint64_t window_word_ops;  /* sum of nw * (2 + 6 d*) */
     uint64_t search_word_ops;  /* sum of n * (2 + 6 d_min) */
@@ -383,7 +385,9 @@ typedef struct {
     uint64_t dc_cycles;        /* shader-clock cycles in DC passes (window setup included), summed over pairs */
     uint64_t tb_cycles;        /* shader-clock cycles in tracebacks and CIGAR stores, summed over pairs */
     uint64_t pair_cycles;      /* shader-clock cycles from a pair's first to last window, summed */
-    uint64_t window_workgroups;/* resident workgroups of the batched window kernel (4 groups each) */
+    uint64_t window_workgroups;/* workgroups of the batched form's window kernel (row tables: the
+                                  resident ones, 4 groups each; one pair per lane: two wavefronts
+                                  each; a batch of few pairs: one pair each); 0 in other forms */
 } genasm_profile;
 
 /* on: 0 = off; 1 = stage times and the per-pair work counters; 2 = stage

@@ -414,7 +414,7 @@ bool lane_path(int commit) { return commit <= kLanePathCommit; }
 // row-table layout, of which this takes a part) or from the context's buffer.
 template <class Mark>
 int align_lanes(genasm_ctx* ctx, AlignParams p, const genasm_launch& L, uint64_t total_read_bases,
-                uint64_t total_ref_bases, Carver* carved, Mark&& mark, hipStream_t s) {
+                uint64_t total_ref_bases, Carver* carved, Mark&& mark, hipStream_t s, int* window_blocks) {
     uint32_t *hist = nullptr, *order = nullptr;
     auto carve = [&](Carver& c) {
         p.search = c.take<SearchOut>(p.n_pairs);
@@ -487,7 +487,7 @@ int align_lanes(genasm_ctx* ctx, AlignParams p, const genasm_launch& L, uint64_t
     CHECK_HIP(ctx, mark(2));
     int blocks = 0;
     CHECK_HIP(ctx, launch_windows_lane(p, max_blocks, &blocks, s));
-    if (ctx->profiling) ctx->prof_window_blocks = blocks;
+    *window_blocks = blocks;
     CHECK_HIP(ctx, launch_audit(p, 1, s));  // debug builds only
     CHECK_HIP(ctx, mark(3));
     return GENASM_OK;
@@ -588,8 +588,11 @@ int align_dev(genasm_ctx* ctx, const uint8_t* d_reads2b, const uint64_t* d_read_
         }
         ctx->prof_pairs = counters ? n_pairs : 0;
         ctx->prof_form = L.form;
+        ctx->prof_window_blocks = 0;
         ctx->have_profile = true;
     }
+    int unprofiled = 0;
+    int& window_blocks = profiling ? ctx->prof_window_blocks : unprofiled;
     auto mark = [&](int i) -> hipError_t {
         return profiling ? hipEventRecord(ctx->ev[i], s) : hipSuccess;
     };
@@ -637,6 +640,7 @@ int align_dev(genasm_ctx* ctx, const uint8_t* d_reads2b, const uint64_t* d_read_
     // The same kernel for a batched launch, where a reference of more than
     // kWaveOwnCols columns is searched by more wavefronts than its pair's.
     auto plain_chunked = [&]() -> int {
+        window_blocks = (int)n_pairs;
         if (total_ref_bases <= kWaveOwnCols) return plain();
         const uint64_t tails = total_ref_bases >> 10;
         const size_t bytes = tails * sizeof(SearchTailSlot);
@@ -717,7 +721,7 @@ int align_dev(genasm_ctx* ctx, const uint8_t* d_reads2b, const uint64_t* d_read_
     if (lanes && !noalloc) {
         // no spill, no item lists; the no-allocation call keeps the layout below, so
         // that it takes the same batches as ever
-        return align_lanes(ctx, p, L, total_read_bases, total_ref_bases, nullptr, mark, s);
+        return align_lanes(ctx, p, L, total_read_bases, total_ref_bases, nullptr, mark, s, &window_blocks);
     }
     if (per_cu == 0) {
         // as many as stay resident together (LDS and registers), so that no
@@ -739,11 +743,11 @@ int align_dev(genasm_ctx* ctx, const uint8_t* d_reads2b, const uint64_t* d_read_
         if (rc) return rc;
         base = ctx->scratch;
     }
-    if (profiling) ctx->prof_window_blocks = win_blocks;
+    window_blocks = win_blocks;
     Carver real{base};
     real.off = base_off;
     if (waves) return plain_chunked();
-    if (lanes) return align_lanes(ctx, p, L, total_read_bases, total_ref_bases, &real, mark, s);
+    if (lanes) return align_lanes(ctx, p, L, total_read_bases, total_ref_bases, &real, mark, s, &window_blocks);
     auto [items, hist, order] = carve(real, workers);
 
     CHECK_HIP(ctx, mark(0));

@@ -393,15 +393,17 @@ __device__ __forceinline__ int wave_trace(const WaveWindow<SETS>& w, const uint8
     return n + rest;
 }
 
-// A window: distance (-1: above K) and, when it is solved, its traceback.
-template <int SETS>
+// A window: distance (-1: above K) and, when it is solved, its traceback. STATS:
+// `solved` is the clock between the two.
+template <int SETS, bool STATS>
 __device__ __forceinline__ int wave_solve(u64 pl, u64 ph, u64 tl, u64 th, int mw, int nw, int K, int L,
                                           uint8_t* lev, int lane, WaveRuns& runs, int& edits, int& i_end,
-                                          int& j_end, bool& exact) {
+                                          int& j_end, bool& exact, u64& solved) {
     WaveWindow<SETS> w;
     wave_window<SETS>(w, pl, ph, tl, th, nw, lane);
     const int d_max = SETS == 1 ? min(K, 63 - kBandBelow) : K;
     const int d = wave_levels<SETS>(w, lev, mw, d_max, lane);
+    if constexpr (STATS) solved = clock64();
     exact = SETS == 2;
     if (SETS == 1) {
         // no answer within K edits is one too when the band holds all of them
@@ -509,7 +511,12 @@ __device__ __forceinline__ void wave_pair_windows(const AlignParams& P, uint64_t
     wave_seq_open(rd, P.reads, pc.rb, pc.m, pj, lane);
     wave_seq_open(rf, P.refs, pc.fb, pc.n, ti, lane);
     bool failed = false, internal = false, park = false;
-    u64 st_wops = 0, st_cells = 0, st_table = 0, st_tb = 0, st_steps = 0;
+    u64 st_wops = 0, st_cells = 0, st_table = 0, st_tb = 0, st_steps = 0, cyc_dc = 0, cyc_tb = 0;
+    u64 cyc_start = 0, wall_start = 0;
+    if constexpr (STATS) {
+        cyc_start = clock64();
+        wall_start = wall_clock64();
+    }
     // every window commits at least one base, so a pair has at most m + n
     const uint32_t max_windows = (uint32_t)pc.m + (uint32_t)pc.n;
     while (pj < pc.m && !park) {
@@ -524,6 +531,8 @@ __device__ __forceinline__ void wave_pair_windows(const AlignParams& P, uint64_t
         }
         ++nwin;
         ++done_here;
+        u64 cyc0 = 0, solved = 0;
+        if constexpr (STATS) cyc0 = solved = clock64();
         wave_seq_window(rd, pj, lane, pl, ph);
         wave_seq_window(rf, ti, lane, tl, th);
         int edits = 0, i_end = 0, j_end = 0, d;
@@ -533,11 +542,15 @@ __device__ __forceinline__ void wave_pair_windows(const AlignParams& P, uint64_t
             if (d >= 0) wave_run(runs, (int)GENASM_OP_INS, edits, lane);
         } else {
             bool exact = false;
-            d = wave_solve<1>(pl, ph, tl, th, mw, nw, P.K, P.L, lev, lane, runs, edits, i_end, j_end, exact);
+            d = wave_solve<1, STATS>(pl, ph, tl, th, mw, nw, P.K, P.L, lev, lane, runs, edits, i_end, j_end, exact,
+                                     solved);
             if (!exact)
-                d = wave_solve<2>(pl, ph, tl, th, mw, nw, P.K, P.L, lev, lane, runs, edits, i_end, j_end, exact);
+                d = wave_solve<2, STATS>(pl, ph, tl, th, mw, nw, P.K, P.L, lev, lane, runs, edits, i_end, j_end, exact,
+                                         solved);
         }
         if constexpr (STATS) {
+            cyc_dc += solved - cyc0;
+            cyc_tb += clock64() - solved;
             st_cells += (u64)mw * nw;
             st_steps += (u64)nw;
         }
@@ -584,6 +597,11 @@ __device__ __forceinline__ void wave_pair_windows(const AlignParams& P, uint64_t
         stp[kStatTbReads] += st_tb;
         stp[kStatWindowLaneSteps] += st_steps;
         stp[kStatWindows] += nwin;
+        stp[kStatDcCycles] += cyc_dc;
+        stp[kStatTbCycles] += cyc_tb;
+        stp[kStatPairCycles] += clock64() - cyc_start;
+        stp[kStatPairStart] = wall_start;
+        stp[kStatPairEnd] = wall_clock64();
     }
     if constexpr (SERVE) {
         P.state[pair] = PairState{ti, pj, score, nwin, runs.written, runs.cur_op, runs.cur_len,

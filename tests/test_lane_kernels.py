@@ -155,3 +155,36 @@ def test_rounds_of_one_window():
             got = results(*ctx.align(reads, refs, 64, launch=launch))
             bad = [i for i in range(len(reads)) if got[i] != want[i]]
             assert not bad, (lpt, len(bad), bad[:5], got[bad[0]], want[bad[0]])
+
+
+@pytest.mark.gpu
+def test_profile_of_every_path():
+    # one pair per wavefront (plain, and a batch of few pairs), one pair per lane with
+    # the longest pairs on wavefronts: every pair's cycles and clocks, the workgroups
+    few = pairs_of(40, 91, [300, 700], [400, 800])
+    many = pairs_of(4500, 92, [60, 90], [80, 110])
+    for i in range(0, 4500, 300):  # longer than twice the mean
+        many[0][i] = gen.random_bases(gen.pair_rng(93, i), 1200)
+        many[1][i] = many[0][i].copy()
+    with ga.Context(0) as ctx:
+        ctx.profile(1)
+        for (reads, refs), form, blocks in ((many, ga.FORM_BATCHED, None), (few, ga.FORM_BATCHED, 40),
+                                            (few, ga.FORM_PLAIN, 0), (few, ga.FORM_UNIMPROVED, 0)):
+            res, _ = ctx.align(reads, refs, 64, launch=ga.make_launch(form))
+            p, w = ctx.profile_read(), ctx.profile_pairs()
+            word = dict(zip(ctx.PROFILE_FIELDS, w.T))
+            assert (word["windows"] == res["n_windows"]).all() and p["windows"] == int(res["n_windows"].sum())
+            assert p["window_workgroups"] == blocks if blocks is not None else 0 < p["window_workgroups"] < 4500
+            if form == ga.FORM_UNIMPROVED:
+                continue
+            ran = res["n_windows"] > 0
+            for name in ("dc_cycles", "tb_cycles", "start_clock"):
+                assert (word[name][ran] > 0).all(), (len(reads), form, name)
+            assert (word["pair_cycles"][ran] >= word["dc_cycles"][ran]).all()
+            assert (word["end_clock"][ran] >= word["start_clock"][ran]).all()
+        # a call without profiling leaves the last profiled call's figures
+        want = ctx.profile_read()
+        ctx.profile(0)
+        ctx.align(*many, 64)
+        ctx.profile(1)
+        assert ctx.profile_read()["window_workgroups"] == want["window_workgroups"]
