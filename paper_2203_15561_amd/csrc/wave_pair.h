@@ -272,9 +272,10 @@ constexpr int kEditDel = (int)GENASM_OP_DEL << kEditOp | 1 << kEditText | -(1 <<
 // is the number of runs before it and its length the distance to the next start.
 __device__ __forceinline__ void wave_edits(WaveRuns& r, int n, int edit, int lane) {
     const int op = (edit >> kEditOp) & 3, i = edit & 63;
-    // behind the edit before; kept out of the subtraction, since the reversed
-    // subtraction it would be folded into as its shifted operand gives the
-    // negative result here
+    // behind the edit before; kept out of the subtraction, which the compiler would
+    // make a v_subrev_u32_dpp of: on this card that gives shifted(s1) - s0 where s1 -
+    // shifted(s0) is meant (with s1 = 10000 (lane + 1) and s0 = 100 + lane, lane 2
+    // got 20000 - 102, not 30000 - 101)
     const int after = (int)here((uint32_t)lane_below0(i + ((edit >> kEditText) & 1), lane));
     const int matches = i - after;
     const bool have = lane < n;

@@ -5,7 +5,9 @@ into inline assembly. Checked in program order over every kernel:
     vector instruction two wait states later at the earliest, and as the lane
     number of a lane read or write four;
   - a vector register is read by a lane read one wait state after a vector
-    instruction wrote it, and as the shifted operand of a lane move (DPP) two."""
+    instruction wrote it, and as the shifted operand of a lane move (DPP) two.
+And no reversed instruction (v_subrev and the like) takes a shifted operand: here
+d = v_subrev_u32_dpp(s0, s1) gave shifted(s1) - s0, not s1 - shifted(s0)."""
 import re
 
 import pytest
@@ -79,3 +81,9 @@ def test_checker_sees_missing_waits():
 def test_no_missing_waits(device_asm):  # noqa: F811
     bad = missing_waits(device_asm)
     assert not bad, (len(bad), bad[:3])
+
+
+def test_no_reversed_lane_moves(device_asm):  # noqa: F811
+    # what the compiler makes of x - lane_below(y), unless here() keeps it apart
+    found = re.findall(r"\bv_\w*rev\w*_dpp\b[^\n]*", device_asm)
+    assert not found, found[:3]
