@@ -2,9 +2,14 @@
 emulation with its sanitizers at launches of few workgroups, so that a
 workgroup takes several rounds of pairs, and on the GPU through the launch
 fields that lead there."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
+import oracle
 import paper_2203_15561_amd as ga
 from tests.emu import run as emu
 from tests.test_pair_paths import expected_of, pairs_of
@@ -14,6 +19,11 @@ from workloads import gen
 @pytest.fixture(scope="module")
 def driver(tmp_path_factory):
     return emu.build(str(tmp_path_factory.mktemp("emu") / "emu_driver"))
+
+
+@pytest.fixture(scope="module")
+def debug_driver(tmp_path_factory):
+    return emu.build(str(tmp_path_factory.mktemp("emu") / "emu_driver_debug"), debug=True)
 
 
 def results(res, cig):
@@ -78,6 +88,94 @@ def test_long_references_emulated(driver):
             assert results(*emu.run(driver, ps, 0, own_cols=own)) == want, (k, own)
             assert results(*emu.run(driver, ps, emu.LANES, pair_lanes=32, own_cols=own)) == want, (k, own)
         assert results(*emu.run(driver, ps, emu.LANES, pair_lanes=32, search_parts_log=1, own_cols=512)) == want, k
+
+
+def mixed_batch(n, seed, longest=400):
+    """Pairs of pairs_of around the windows' edges, every 16th read long."""
+    reads, refs = pairs_of(n, seed, [150, 0, 39, 40, 41, 64, 65, 104, 81], [170, 64, 0, 129, 250, 90])
+    for i in range(0, n, 16):
+        rng = gen.pair_rng(seed + 1, i)
+        reads[i] = gen.random_bases(rng, longest)
+        refs[i] = gen.mutate(rng, reads[i], 0.1, (0.15, 0.5, 0.35)) if i % 48 else gen.random_bases(rng, longest)
+    return reads, refs
+
+
+@pytest.mark.slow
+@pytest.mark.parametrize("W,O,k", [(64, 24, 64), (64, 24, 5), (33, 9, 64), (8, 7, 3)])
+def test_batches_emulated(driver, debug_driver, W, O, k):
+    # several rounds of full and part wavefronts, the longest pairs on wavefronts of
+    # their own, several search parts a pair; the debug build's checks and its audit
+    # that every pair is taken once
+    ps = gen.from_lists("mixed", *mixed_batch(72, 51), k, W, O)
+    want = expected_of(ps)
+    for kw in (dict(pair_lanes=8, window_blocks=3, turned_from=1), dict(pair_lanes=64, long_pairs=5, long_bases=200),
+               dict(pair_lanes=16, long_pairs=3, long_bases=200, search_parts_log=2)):
+        for build in (driver, debug_driver):
+            assert results(*emu.run(build, ps, emu.LANES, **kw)) == want, kw
+
+
+@pytest.mark.slow
+@pytest.mark.parametrize("slots,admit", [(3, 2), (60, 60)])
+@pytest.mark.parametrize("budget,ticks", [(0, 40), (2, 0)])
+def test_serving_emulated(driver, slots, admit, budget, ticks):
+    # few resident pairs, a wavefront each (up to two a workgroup), and more, a lane
+    # each; turns that end by time and by windows
+    reads, refs = mixed_batch(60 if slots > 3 else 14, 52, 300)
+    for k, W, O in ((64, 64, 24), (5, 16, 8)):
+        ps = gen.from_lists("serve", reads, refs, k, W, O)
+        got = results(*emu.run(driver, ps, emu.SERVE_LANES, window_blocks=2, slots=slots, admit_per_iteration=admit,
+                               window_budget=budget, ticks=ticks, search_chunk=64, turned_from=1))
+        assert got == expected_of(ps), (k, W, O)
+
+
+@pytest.mark.gpu
+def test_launch_fields_and_counters_of_lanes():
+    # a batch too large for a wavefront a pair: the launch fields that keep it on
+    # lanes, and the work counters against the oracle's
+    reads, refs = mixed_batch(4600, 53, 3000)
+    ps = gen.from_lists("mixed", reads, refs, 64)
+    res_o, _, _, _ = oracle.batch(ps)
+    want = expected_of(ps)
+    with ga.Context(0) as ctx:
+        for kw in ({}, dict(workers_per_cu=1), dict(lpt_order=0), dict(workers_per_cu=2, lpt_order=0)):
+            ctx.profile(1)
+            got = results(*ctx.align(reads, refs, 64, launch=ga.make_launch(ga.FORM_BATCHED, **kw)))
+            p = ctx.profile_read()
+            assert got == want, kw
+            # two wavefronts a workgroup, not the row tables' resident grid
+            assert 0 < p["window_workgroups"] <= 256 * (kw.get("workers_per_cu") or 4), kw
+            for name, field in (("window_cells", "cells_window"), ("search_cells", "cells_search"), ("windows", "n_windows"),
+                                ("window_word_ops", "word_ops"), ("table_words", "words_stored")):
+                assert p[name] == int(res_o[field].sum()), (kw, name)
+            ctx.profile(0)
+            assert results(*ctx.align(reads, refs, 64, launch=ga.make_launch(ga.FORM_BATCHED, **kw))) == want, kw
+
+
+CHILD = r"""
+import paper_2203_15561_amd as ga
+from paper_2203_15561_amd import capi
+from tests.test_lane_kernels import mixed_batch, results, rounds_of_pairs
+from tests.test_pair_paths import expected_of
+from workloads import gen
+
+assert capi.LIB_PATH.endswith("libgenasm_debug.so"), capi.LIB_PATH
+with ga.Context(0) as ctx:
+    for name, (reads, refs) in (("mixed", mixed_batch(4600, 54, 2000)), ("one window", rounds_of_pairs(17_000, 55))):
+        want = expected_of(gen.from_lists(name, reads, refs, 64))
+        for kw in ({}, dict(workers_per_cu=1), dict(lpt_order=0)):
+            print("debug build:", name, kw, flush=True)
+            assert results(*ctx.align(reads, refs, 64, launch=ga.make_launch(ga.FORM_BATCHED, **kw))) == want
+print("all clean", flush=True)
+"""
+
+
+@pytest.mark.gpu
+def test_debug_build_on_lanes():
+    # every pair taken by exactly one lane or wavefront (flags are 0 in results())
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-u", "-c", CHILD], cwd=root, env=dict(os.environ, GENASM_LIB_VARIANT="debug"),
+                       timeout=100, capture_output=True, text=True)
+    assert r.returncode == 0 and "all clean" in r.stdout, r.stdout[-2000:] + r.stderr[-4000:]
 
 
 @pytest.mark.gpu
