@@ -3,9 +3,10 @@
 
 One step = the whole path over one batch already resident in device memory:
 2-bit packing of the ASCII reads and references, the start search, and the
-windowed DC + traceback with run-length CIGAR output (batched form: search
-kernels, then the persistent window kernel with its work queue). Prints ONE
-JSON line on stdout; progress goes to stderr.
+windowed DC + traceback with run-length CIGAR output (batched form: the start
+search and the windows with one pair per lane, unless a launch's fields or the
+autotuner ask for the row-table kernels). Prints ONE JSON line on stdout;
+progress goes to stderr.
 
 Default workload: 20,000 pairs of 10 kb reads with 10% PacBio-like edits,
 reference = true segment +-500 bp, 30% unrelated 10 kb decoys, k=64, W=64,
@@ -35,7 +36,32 @@ INT32_PEAK_TOPS = 256 * 128 * 2.4e9 / 1e12
 # scaled by a copy kernel of known size; valid only for the kernel source it was
 # measured on.
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_windows_long10k_traffic.json")
-KERNEL_SRC = os.path.join(ROOT, "paper_2203_15561_amd", "csrc", "kernels.hip")
+KERNEL_SRCS = [os.path.join(ROOT, "paper_2203_15561_amd", "csrc", f)
+               for f in ("kernels.hip", "lanes.h", "diff_window.h", "wave_pair.h", "filter.h")]
+
+# 32-bit operations of one text column of a window's dynamic program on vertical
+# differences: 17 on 64-bit words (the published bit-vector recurrence for
+# approximate matching), for 64 cells
+COLUMN_OPS = 34
+
+
+def window_kernel(launch, pr, commit):
+    """(name, 32-bit operations) of the window kernel that a batched launch took,
+    from its profile `pr` (commit: W - O): the recurrence the kernel computes, its
+    traceback not counted. The row tables compute nw * (2 + 6 d*) 64-bit words a
+    window; one pair per lane computes the columns of differences whatever d* is;
+    one pair per wavefront computes levels, which have no count of their own here."""
+    import paper_2203_15561_amd as ga
+    base = ga.default_launch(ga.FORM_BATCHED)
+    geometry = ("group_lanes", "search_lanes", "lds_rows", "hard_row", "hard_lanes", "tb_prefetch",
+                "hard_share", "table_bits", "search_per_cu")
+    if all(getattr(launch, f) in (0, getattr(base, f)) or (getattr(launch, f) < 0 and f != "hard_row")
+           for f in geometry):
+        if pr["window_workgroups"] == pr["n_pairs"]:
+            return "k_pair_wave (search, windows, traceback)", None
+        if commit <= 40:
+            return "k_windows_lane (window DC + traceback)", pr["window_cells"] * COLUMN_OPS // 64
+    return "k_windows (window DC + traceback)", 2 * pr["window_word_ops"]
 
 
 def measured_traffic(workload: str):
@@ -43,8 +69,7 @@ def measured_traffic(workload: str):
     try:
         with open(TRAFFIC_FILE) as f:
             rec = json.load(f)
-        with open(KERNEL_SRC, "rb") as f:
-            src_hash = hashlib.sha256(f.read()).hexdigest()
+        src_hash = hashlib.sha256(b"".join(open(f, "rb").read() for f in KERNEL_SRCS)).hexdigest()
     except (OSError, ValueError):
         return None
     if rec.get("kernels_sha256") != src_hash or rec.get("workload") != workload:
@@ -67,16 +92,20 @@ def rle(ops: str) -> str:
     return "".join(out)
 
 
-def measured_peaks(ctx, achieved):
+def measured_peaks(ctx, achieved, row_tables):
     """The device limits measured by the library's microbenchmarks, and the
-    window kernel's rate against the recurrence's own instruction mix."""
+    window kernel's rate against them (`dc_mix`: the row recurrence's own
+    instruction mix, for the kernels that compute it)."""
     pk = ctx.measure_peaks()
-    return {"dc_mix_tops": pk["dc_mix_tops"], "int32_tops": pk["int32_tops"],
-            "lds_tbps": pk["lds_tbps"], "hbm_tbps": pk["hbm_tbps"],
-            "shift64_tops": pk["shift64_tops"], "funnel_tops": pk["funnel_tops"],
-            "dpp_tops": pk["dpp_tops"],
-            "frac_of_dc_mix": achieved / pk["dc_mix_tops"],
-            "frac_of_int32": achieved / pk["int32_tops"]}
+    out = {"dc_mix_tops": pk["dc_mix_tops"], "int32_tops": pk["int32_tops"],
+           "lds_tbps": pk["lds_tbps"], "hbm_tbps": pk["hbm_tbps"],
+           "shift64_tops": pk["shift64_tops"], "funnel_tops": pk["funnel_tops"],
+           "dpp_tops": pk["dpp_tops"]}
+    if achieved is not None:
+        out["frac_of_int32"] = achieved / pk["int32_tops"]
+        if row_tables:
+            out["frac_of_dc_mix"] = achieved / pk["dc_mix_tops"]
+    return out
 
 
 def provenance(gen, dev):
@@ -442,8 +471,9 @@ def main():
 
     pr = {**prc, **{k: v for k, v in pr.items() if k.endswith("_ms")}}
     cells = pr["window_cells"] + pr["search_cells"]
-    int_ops_windows = 2 * pr["window_word_ops"]  # two 32-bit halves per 64-bit word op
-    achieved = int_ops_windows / (np.mean(win_ms) / 1e3) / 1e12
+    kernel, int_ops_windows = window_kernel(batched, pr, ps.W - ps.O)
+    achieved = int_ops_windows / (np.mean(win_ms) / 1e3) / 1e12 if int_ops_windows else None
+    row_tables = kernel.startswith("k_windows ")
     line = {
         "metric": "alignments/s (10 kb reads, 10% edits, batched form)",
         "value": ps.n_pairs / (ms_step / 1e3),
@@ -469,12 +499,15 @@ def main():
         "gcups": cells / (ms_step / 1e3) / 1e9,
         "window_kernel_ms": float(np.mean(win_ms)),
         "search_ms": float(np.mean(search_ms)),
-        "roofline": {"bound": "alu", "kernel": "k_windows_lane (window DC + traceback)",
+        "roofline": {"bound": "alu", "kernel": kernel,
                      "achieved": achieved, "peak": INT32_PEAK_TOPS, "unit": "TOP/s",
-                     "frac": achieved / INT32_PEAK_TOPS, "traffic": None,
+                     "frac": achieved / INT32_PEAK_TOPS if achieved is not None else None,
+                     "traffic": None,
                      "ops_per_launch": int_ops_windows,
+                     "ops_basis": "2 x window_word_ops" if row_tables else
+                                  f"{COLUMN_OPS} per 64 window cells, traceback not counted",
                      "peak_basis": "256 CUs x 128 int32 lanes per cycle x 2.4 GHz",
-                     "measured": measured_peaks(ctx, achieved)},
+                     "measured": measured_peaks(ctx, achieved, row_tables)},
         "work": {k: int(v) for k, v in pr.items() if not k.endswith("_ms")},
         "verified_pairs": verified,
         "provenance": provenance(gen, dev),
@@ -532,6 +565,10 @@ def main():
             "footprint_reduction": (pu["table_words"] / max(pu["windows"], 1)) / (pr["table_words"] / win),
             "access_reduction": (pu["table_words"] + pu["tb_reads"]) / (pr["table_words"] + pr["tb_reads"]),
             "dc_work_reduction": pu["window_word_ops"] / max(pr["window_word_ops"], 1),
+            # table_words, tb_reads and window_word_ops are those of the row tables; a
+            # launch with one pair per lane or wavefront keeps none and reports them
+            # for comparison
+            "counters_modelled": not row_tables,
             "paper": {"footprint_reduction": 24, "access_reduction": 12, "gpu_speedup": 5.9},
         }
         log(f"unimproved: {um:.1f} ms/step ({um / ms_step:.1f}x the batched step); footprint "

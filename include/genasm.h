@@ -364,6 +364,11 @@ int genasm_validate(const char* reads, uint64_t reads_len, const uint64_t* read_
  * its pairs. Counters follow the GenASM recurrence: a DC window costs
  * nw * (2 + 6 d*) 64-bit word operations (row 0: shift, or; rows 1..d*:
  * and, shift, or, shift, and, and), the start search n * (2 + 6 d_min).
+ * The launches that keep no row tables (one pair per wavefront or lane, see
+ * GENASM_FORM_*) compute the same cells in another way: there the word
+ * operations, table_words, tb_reads (two a committed edit) and
+ * window_lane_steps (nw a window) are what a row table would take for these
+ * windows, for comparison, and not the kernel's own work.
  */
 typedef struct {
     float total_ms;            /* first to last kernel of the call */
