@@ -148,7 +148,8 @@ struct AlignParams {
     int32_t route;              // search: append finished pairs to the window lists
     int32_t compact;            // window kernel: compact 16-lane groups (32-bit table slices)
     int32_t pair_lanes;         // one pair per lane: lanes of a wavefront that take a pair
-    int32_t turned_from;        // there: the first workgroup whose wavefronts change roles
+    int32_t alone;              // there: at most two workgroups a compute unit, a SIMD a wavefront
+    uint32_t* cu_roles;         // there, otherwise: kCuRoles words, which roles are on which SIMD
     int32_t long_pairs;         // there: at most so many first pairs of `order` take a wavefront
     int32_t long_bases;         // each, as far as their reads are longer than this
     int32_t search_parts_log;   // one search part per lane: log2 of a pair's parts
@@ -284,6 +285,7 @@ hipError_t launch_audit(const AlignParams& p, int queued, hipStream_t s);
 // The one-pair-per-lane path (lanes.h): planes of both streams and cleared
 // search keys, the start search, the windows (max_blocks workgroups at most, 0
 // = one per p.pair_lanes pairs; *n_blocks receives their number).
+constexpr int kCuRoles = 4096;  // by XCD, shader engine and compute unit
 constexpr int kLanePathCommit = 40;  // its windows commit at most this many bases (W - O)
 hipError_t launch_lane_prep(const AlignParams& p, uint64_t n_read, uint64_t n_ref, hipStream_t s);
 hipError_t launch_search_lane(const AlignParams& p, hipStream_t s);

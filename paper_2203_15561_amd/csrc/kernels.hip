@@ -2503,11 +2503,12 @@ hipError_t launch_search_finalize(const AlignParams& p, uint32_t max_pairs, hipS
 
 hipError_t launch_lane_prep(const AlignParams& p, uint64_t n_read, uint64_t n_ref, hipStream_t s) {
     const uint64_t rw = plane_words(n_read), fw = plane_words(n_ref);
-    const uint64_t threads = rw + fw > p.n_pairs ? rw + fw : p.n_pairs;
+    const uint64_t least = p.cu_roles && p.n_pairs < kCuRoles ? kCuRoles : p.n_pairs;
+    const uint64_t threads = rw + fw > least ? rw + fw : least;
     hipLaunchKernelGGL(k_lane_prep, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, p.reads,
                        p.read_off, n_read, const_cast<u64*>(p.read_lo), const_cast<u64*>(p.read_hi), rw,
                        p.refs, p.ref_off, n_ref, const_cast<u64*>(p.ref_lo), const_cast<u64*>(p.ref_hi),
-                       fw, p.search_key, p.n_pairs);
+                       fw, p.search_key, p.n_pairs, p.cu_roles);
     return hipGetLastError();
 }
 
@@ -2523,7 +2524,7 @@ hipError_t launch_search_lane_items(const AlignParams& p, int blocks, hipStream_
 }
 
 hipError_t launch_windows_serve(const AlignParams& p, int blocks, hipStream_t s) {
-    hipLaunchKernelGGL((k_windows_lane<false, true>), dim3(blocks), dim3(128), kLaneLdsBytes, s, p);
+    hipLaunchKernelGGL((k_windows_lane<false, true, true>), dim3(blocks), dim3(128), kLaneLdsBytes, s, p);
     return hipGetLastError();
 }
 
@@ -2532,8 +2533,14 @@ hipError_t launch_windows_lane(const AlignParams& p, uint64_t max_blocks, int* n
     const unsigned blocks = (unsigned)(max_blocks && want > max_blocks ? max_blocks : want);
     const dim3 grid(blocks), block(128);
     *n_blocks = (int)blocks;
-    if (p.stats) hipLaunchKernelGGL((k_windows_lane<true, false>), grid, block, kLaneLdsBytes, s, p);
-    else hipLaunchKernelGGL((k_windows_lane<false, false>), grid, block, kLaneLdsBytes, s, p);
+    if (p.alone) {
+        if (p.stats) hipLaunchKernelGGL((k_windows_lane<true, false, true>), grid, block, kLaneLdsBytes, s, p);
+        else hipLaunchKernelGGL((k_windows_lane<false, false, true>), grid, block, kLaneLdsBytes, s, p);
+    } else if (p.stats) {
+        hipLaunchKernelGGL((k_windows_lane<true, false, false>), grid, block, kLaneLdsBytes, s, p);
+    } else {
+        hipLaunchKernelGGL((k_windows_lane<false, false, false>), grid, block, kLaneLdsBytes, s, p);
+    }
     return hipGetLastError();
 }
 

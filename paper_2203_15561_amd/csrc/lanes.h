@@ -449,8 +449,55 @@ __device__ __forceinline__ void windows_write(const AlignParams& P, const LaneSh
     }
 }
 
-// A workgroup's LDS: the mail, or the levels of its two wavefronts.
+// A workgroup's LDS: the mail and its roles, or the levels of its two wavefronts.
 constexpr int kLaneLdsBytes = 2 * kWaveLdsBytes;
+constexpr int kRolesAt = kLaneLdsBytes / 4 - 4;  // words: two SIMDs, the role, the claim
+static_assert(sizeof(LaneMail) <= 4 * kRolesAt, "layout");
+
+// Which wavefront of a workgroup computes, where three or four workgroups share a
+// compute unit: the SIMDs that its wavefronts get depend on what ran there before,
+// and two computing wavefronts on one SIMD take longer than one of each. A word per
+// compute unit counts the roles on its SIMDs (a byte each: computing, and writing
+// from bit 4 on); a workgroup claims the better of its two ways round. The words
+// steer only: whatever they hold, a workgroup has one wavefront of each kind.
+__device__ __forceinline__ uint32_t* cu_word(const AlignParams& P, uint32_t& simd) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    // HW_ID: SIMD in bits 4..5, compute unit and shader engine in 8..15; XCC_ID
+    const uint32_t id = __builtin_amdgcn_s_getreg(4 | 31 << 11), xcd = __builtin_amdgcn_s_getreg(20 | 31 << 11);
+#else
+    const uint32_t id = ((blockIdx.x + (threadIdx.x >> 6)) & 3u) << 4, xcd = 0u;
+#endif
+    simd = (id >> 4) & 3u;
+    return P.cu_roles + (((id >> 8) & 0xFFu) | (xcd & 15u) << 8);
+}
+__device__ __forceinline__ int claim_roles(const AlignParams& P, uint32_t* roles, int wave, int lane) {
+    uint32_t simd;
+    uint32_t* word = cu_word(P, simd);
+    if (lane == 0) roles[wave] = simd;
+    mail_barrier();
+    if (wave == 0 && lane == 0) {
+        const uint32_t a = 8u * roles[0], b = 8u * roles[1];
+        const uint32_t first = (1u << a) + (16u << b), second = (1u << b) + (16u << a);
+        const uint32_t old = atomicAdd(word, first);
+        // two computing wavefronts on a SIMD are the worst, two writing ones leave a
+        // later workgroup no better place
+        auto load = [&](uint32_t compute, uint32_t write) {
+            const uint32_t c = old >> compute, w = old >> write;
+            return 4u * (c & 15u) + ((c >> 4) & 15u) + (w & 15u) + 2u * ((w >> 4) & 15u);
+        };
+        const bool turned = load(b, a) < load(a, b);
+        if (turned) atomicAdd(word, second - first);
+        roles[2] = turned ? 1u : 0u;
+        roles[3] = turned ? second : first;
+    }
+    mail_barrier();
+    return uniform((int)roles[2]);
+}
+__device__ __forceinline__ void release_roles(const AlignParams& P, const uint32_t* roles, int lane) {
+    uint32_t simd;
+    uint32_t* word = cu_word(P, simd);
+    if (lane == 0) atomicAdd(word, 0u - roles[3]);
+}
 
 // Window kernel, two wavefronts per workgroup and one pair per lane of them:
 // one computes the windows, the other turns each window's path into CIGAR runs
@@ -462,10 +509,19 @@ constexpr int kLaneLdsBytes = 2 * kWaveLdsBytes;
 // therefore take the longest pairs a wavefront each, if the lengths are uneven
 // (wave_pair.h: 1.7 us a window); so do all workgroups of a serving iteration with no more
 // resident pairs than wavefronts.
-template <bool STATS, bool SERVE>
-__global__ __launch_bounds__(128, 2) void k_windows_lane(AlignParams P) {
+//
+// ALONE: a wavefront takes more than half of a SIMD's registers, so that no two
+// share one. Where a compute unit's next workgroup starts is not fixed (most often on
+// a free pair of SIMDs or with the last one's second, now and then with its first),
+// and a computing wavefront that shares its SIMD takes 1.7 times as long, and the
+// batch with it (30,000 pairs of 10 kb: windows 1.37 ms, 2.35 when the roles went by
+// the workgroup's number and one unit in a hundred had two of them on a SIMD).
+template <bool STATS, bool SERVE, bool ALONE>
+__global__ __launch_bounds__(128, ALONE ? 1 : 2) void k_windows_lane(AlignParams P) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (ALONE) asm volatile("" : : : "a127");
+#endif
     extern __shared__ u64 smem[];
-    static_assert(sizeof(LaneMail) <= kLaneLdsBytes, "layout");
     const int lane = threadIdx.x & 63, wave = uniform((int)(threadIdx.x >> 6));
     uint8_t* lev = reinterpret_cast<uint8_t*>(smem) + wave * kWaveLdsBytes;
     const LaneShare share = lane_share<SERVE>(P, lane);
@@ -480,8 +536,12 @@ __global__ __launch_bounds__(128, 2) void k_windows_lane(AlignParams P) {
         return;
     }
     LaneMail& mail = *reinterpret_cast<LaneMail*>(smem);
-    if (wave == ((int)blockIdx.x >= P.turned_from ? 1 : 0)) windows_compute<STATS, SERVE>(P, share, mail, lane);
+    const bool claim = !SERVE && !ALONE && P.cu_roles && share.first < share.n;
+    uint32_t* roles = reinterpret_cast<uint32_t*>(smem) + kRolesAt;
+    const int computes = claim ? claim_roles(P, roles, wave, lane) : 0;
+    if (wave == computes) windows_compute<STATS, SERVE>(P, share, mail, lane);
     else windows_write<STATS, SERVE>(P, share, mail, lane);
+    if (claim && wave == computes) release_roles(P, roles, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -630,9 +690,11 @@ __global__ __launch_bounds__(64) void k_search_lane_items(AlignParams P) {
 
 __global__ void k_lane_prep(const uint8_t* reads, const uint64_t* d_read, uint64_t n_read, u64* rlo,
                             u64* rhi, uint64_t rw, const uint8_t* refs, const uint64_t* d_ref,
-                            uint64_t n_ref, u64* flo, u64* fhi, uint64_t fw, u64* key, uint64_t n_pairs) {
+                            uint64_t n_ref, u64* flo, u64* fhi, uint64_t fw, u64* key, uint64_t n_pairs,
+                            uint32_t* cu_roles) {
     const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t < n_pairs) key[t] = ~0ull;
+    if (cu_roles && t < kCuRoles) cu_roles[t] = 0u;
     const bool rd = t < rw;
     const uint64_t w = rd ? t : t - rw;
     if (!rd && w >= fw) return;

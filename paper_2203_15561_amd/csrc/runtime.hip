@@ -421,6 +421,7 @@ int align_lanes(genasm_ctx* ctx, AlignParams p, const genasm_launch& L, uint64_t
         p.search_key = c.take<unsigned long long>(p.n_pairs);
         hist = c.take<uint32_t>(kLptBuckets);
         order = c.take<uint32_t>(p.n_pairs);
+        p.cu_roles = c.take<uint32_t>(kCuRoles);
     };
     if (carved) {
         carve(*carved);
@@ -451,19 +452,21 @@ int align_lanes(genasm_ctx* ctx, AlignParams p, const genasm_launch& L, uint64_t
     p.search_own = (uint64_t)p.search_part_cols << p.search_parts_log;
     if (total_ref_bases > p.search_own) p.search_tails = total_ref_bases >> p.search_tail_log;
     // Pairs per wavefront: as few as leave every SIMD one wavefront (a workgroup
-    // has two). A SIMD with one wavefront already issues at nine tenths of its
-    // rate, so sharing SIMDs costs time: 20,000 pairs of 10 kb took 1.8 ms 64 to
-    // a wavefront and 2.9 ms 32 to a wavefront.
+    // has two). Most of a window is three-operand instructions, shifts and extracts,
+    // which a wavefront alone on its SIMD issues at nine tenths of the rate of eight,
+    // so sharing SIMDs costs time: windows of 20,000 pairs of 10 kb take 1.32 ms 64 to
+    // a wavefront and 2.03 ms 32 to a wavefront.
     p.pair_lanes = 1;
     while (p.pair_lanes < 64 && (uint64_t)ctx->num_cus * 2 * p.pair_lanes < p.n_pairs) p.pair_lanes *= 2;
-    // A compute unit's next workgroup starts on the SIMD of the last one's second
-    // wavefront. Where two are the most on a unit, the second changes its roles, so
-    // that no computing wavefront shares a SIMD while another SIMD is idle (30,000
-    // pairs of 10 kb: windows 1.62 -> 1.40 ms). With three that puts two computing
-    // ones on a SIMD (40,000: 2.23 -> 2.43), with four there is one of each on
-    // every SIMD as it is.
+    // Up to two workgroups a compute unit have a SIMD for each wavefront; those past
+    // that (the longest pairs' come first) wait for one. With three or four a unit
+    // they share, and each takes the roles that suit the others' (36,000 pairs of 10
+    // kb: 2.50 ms, 2.56 to 2.74 with fixed ones; 60,000 of 1 kb: 353 us against 371).
+    // With more, rounds of them even out and the claims only cost (100,000 of 250
+    // bases: 180 us against 178).
     const uint64_t lane_blocks = (p.n_pairs + p.pair_lanes - 1) / p.pair_lanes;
-    p.turned_from = lane_blocks <= (uint64_t)ctx->num_cus * 2 ? ctx->num_cus : INT32_MAX;
+    p.alone = lane_blocks <= (uint64_t)ctx->num_cus * 2;
+    if (p.alone || lane_blocks > (uint64_t)ctx->num_cus * 4) p.cu_roles = nullptr;
     const uint64_t max_blocks = (uint64_t)ctx->num_cus * L.workers_per_cu;
     if (L.lpt_order && max_blocks == 0) {
         // A batch of uneven lengths ends with its longest chains of windows, and a

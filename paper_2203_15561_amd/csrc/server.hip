@@ -469,7 +469,6 @@ int genasm_server_create(genasm_ctx* ctx, const genasm_server_config* cfg_in,
     p.ref_lo = srv->d_plo;
     p.ref_hi = srv->d_phi;
     p.planes_from_off0 = 0;
-    p.turned_from = ctx->num_cus;  // as with two workgroups a unit in the batched form
     p.read_off = srv->d_read_off;
     p.ref_off = srv->d_ref_off;
     p.read_len = srv->d_read_len;

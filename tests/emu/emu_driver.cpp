@@ -9,7 +9,7 @@
 //      slots, admit_per_iteration, hard_lanes, search_chunk, tb_prefetch, hard_share,
 //      serving window time in emulated clock reads (0 = none), compact window groups (0/1),
 //      pairs a wavefront (5), window workgroups (5: 0 = as many as the pairs take; 6),
-//      the first workgroup with turned roles (5, 6), long_pairs and long_bases (5),
+//      the instance for a SIMD per wavefront (5), long_pairs and long_bases (5),
 //      log2 of a pair's search parts (5), columns of a part (5) or of a pair's own
 //      wavefront (0), longer references in chunks (0 = no limit);
 //      then
@@ -46,7 +46,7 @@ int main(int argc, char** argv) {
     const int hard_share = (int)h[17];
     const uint32_t ticks = (uint32_t)h[18];
     const int compact = (int)h[19];
-    const int pair_lanes = (int)h[20], window_blocks = (int)h[21], turned_from = (int)h[22];
+    const int pair_lanes = (int)h[20], window_blocks = (int)h[21], alone = (int)h[22];
     const int long_pairs = (int)h[23], long_bases = (int)h[24], parts_log = (int)h[25];
     const uint32_t own_cols = (uint32_t)h[26];
     std::vector<uint8_t> reads(nrb + 8), refs(nfb + 8);
@@ -169,7 +169,6 @@ int main(int argc, char** argv) {
         p.window_budget = budget;
         p.search_key = key.data();
         p.search_chunk = chunk;
-        p.turned_from = turned_from;
         p.fin_list = fin.data();
         p.fin_len = fin_len.data();
         uint64_t next = 0, finished_n = 0, iters = 0, resident = 0;
@@ -301,7 +300,9 @@ int main(int argc, char** argv) {
         p.search_key = key.data();
         p.order = order.data();
         p.pair_lanes = pair_lanes;
-        p.turned_from = turned_from;
+        std::vector<uint32_t> cu_roles(kCuRoles, 0x5Au);
+        p.alone = alone;
+        p.cu_roles = alone ? nullptr : cu_roles.data();
         p.long_pairs = long_pairs;
         p.long_bases = long_bases;
         p.search_parts_log = parts_log;
@@ -314,6 +315,9 @@ int main(int argc, char** argv) {
         int used = 0;
         launch_windows_lane(p, (uint64_t)window_blocks, &used, nullptr);
         launch_audit(p, 1, nullptr);  // debug builds only
+        for (const uint32_t r : cu_roles) {
+            if (!alone && r) { fprintf(stderr, "roles left claimed\n"); return 3; }
+        }
         fprintf(stderr, "emu: %d window workgroups\n", used);
     } else if (form == GENASM_FORM_UNIMPROVED) {
         emu::group_lanes = 64;

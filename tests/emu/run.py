@@ -45,14 +45,14 @@ SERVE_LANES = 6  # the serving loop with one pair per lane
 def run(driver: str, ps, form: int, group_lanes=16, search_lanes=16, lds_rows=16, hard_row=16,
         timeout=600, window_budget=0, slots=0, admit_per_iteration=0, hard_lanes=16,
         search_chunk=37, tb_prefetch=0, hard_share=50, ticks=0, compact=1, pair_lanes=64,
-        window_blocks=0, turned_from=1 << 30, long_pairs=0, long_bases=0, search_parts_log=0,
+        window_blocks=0, alone=0, long_pairs=0, long_bases=0, search_parts_log=0,
         own_cols=0):
     """Returns (results, list of (op char, length) runs per pair)."""
     reads2b, refs2b = pack2b(ps.reads), pack2b(ps.refs)
     hdr = np.array([form, group_lanes, search_lanes, lds_rows, ps.k, ps.W, ps.O, ps.n_pairs,
                     len(reads2b), len(refs2b), hard_row, window_budget, slots,
                     admit_per_iteration, hard_lanes, search_chunk, tb_prefetch, hard_share, ticks,
-                    compact, pair_lanes, window_blocks, turned_from, long_pairs, long_bases,
+                    compact, pair_lanes, window_blocks, alone, long_pairs, long_bases,
                     search_parts_log, own_cols],
                    dtype=np.int64)
     with tempfile.TemporaryDirectory() as tmp:

@@ -12,7 +12,7 @@ import re
 
 import pytest
 
-from tests.test_kernel_asm import device_asm  # noqa: F401
+from tests.test_kernel_asm import device_asm, kernel_meta  # noqa: F401
 
 pytestmark = pytest.mark.slow
 
@@ -87,3 +87,13 @@ def test_no_reversed_lane_moves(device_asm):  # noqa: F811
     # what the compiler makes of x - lane_below(y), unless here() keeps it apart
     found = re.findall(r"\bv_\w*rev\w*_dpp\b[^\n]*", device_asm)
     assert not found, found[:3]
+
+
+def test_lone_wavefronts_take_a_simd(device_asm):  # noqa: F811
+    # instances that rely on no two wavefronts fitting a SIMD's 512 registers, and
+    # the ones of which two have to
+    meta = kernel_meta(device_asm)
+    regs = {k: int(re.search(r"\.vgpr_count:\s+(\d+)", v).group(1)) for k, v in meta.items() if "k_windows_lane" in k}
+    alone = {k: v for k, v in regs.items() if "ELb1EEEv" in k}
+    assert len(alone) == 3 and all(v > 256 for v in alone.values()), regs
+    assert len(regs) == 5 and all(v <= 256 for k, v in regs.items() if k not in alone), regs

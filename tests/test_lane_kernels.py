@@ -41,12 +41,11 @@ def rounds_of_pairs(n, seed):
 @pytest.mark.slow
 @pytest.mark.parametrize("k", [64, 3])
 def test_rounds_of_one_window_emulated(driver, k):
-    # 200 pairs on two workgroups of 32 lanes: four rounds; and the other way round
-    # (the second wavefront computes)
+    # 200 pairs on two workgroups of 32 lanes: four rounds
     ps = gen.from_lists("rounds", *rounds_of_pairs(200, 71), k)
     want = expected_of(ps)
-    for turned_from in (1 << 30, 0):
-        got = results(*emu.run(driver, ps, emu.LANES, pair_lanes=32, window_blocks=2, turned_from=turned_from))
+    for alone in (0, 1):
+        got = results(*emu.run(driver, ps, emu.LANES, pair_lanes=32, window_blocks=2, alone=alone))
         assert got == want
 
 
@@ -108,7 +107,7 @@ def test_batches_emulated(driver, debug_driver, W, O, k):
     # that every pair is taken once
     ps = gen.from_lists("mixed", *mixed_batch(72, 51), k, W, O)
     want = expected_of(ps)
-    for kw in (dict(pair_lanes=8, window_blocks=3, turned_from=1), dict(pair_lanes=64, long_pairs=5, long_bases=200),
+    for kw in (dict(pair_lanes=8, window_blocks=3, alone=1), dict(pair_lanes=64, long_pairs=5, long_bases=200),
                dict(pair_lanes=16, long_pairs=3, long_bases=200, search_parts_log=2)):
         for build in (driver, debug_driver):
             assert results(*emu.run(build, ps, emu.LANES, **kw)) == want, kw
@@ -124,7 +123,7 @@ def test_serving_emulated(driver, slots, admit, budget, ticks):
     for k, W, O in ((64, 64, 24), (5, 16, 8)):
         ps = gen.from_lists("serve", reads, refs, k, W, O)
         got = results(*emu.run(driver, ps, emu.SERVE_LANES, window_blocks=2, slots=slots, admit_per_iteration=admit,
-                               window_budget=budget, ticks=ticks, search_chunk=64, turned_from=1))
+                               window_budget=budget, ticks=ticks, search_chunk=64))
         assert got == expected_of(ps), (k, W, O)
 
 
