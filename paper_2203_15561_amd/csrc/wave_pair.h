@@ -631,8 +631,9 @@ __device__ __forceinline__ void wave_pair_from_key(const AlignParams& P, uint64_
                                                    uint8_t* lev, int lane) {
     const int m1 = min(P.W, pc.m);
     const int Kr = min(P.K, m1 - 1);
+    key = (int)(key >> 32) <= Kr ? key : ~0ull;
     int row = -1, col = 0;
-    if (key != ~0ull && (int)(key >> 32) <= Kr) {
+    if (key != ~0ull) {
         row = (int)(key >> 32);
         col = (int)(uint32_t)key;
     } else if (m1 <= P.K) {
