@@ -111,9 +111,12 @@ typedef struct {
     int32_t search_lanes;    /* batched: lanes per pair in the start search, 16 or 64; 0 = default */
     int32_t lds_rows;        /* batched: window-table rows kept in LDS per 16-lane group
                                 (16, 32, 48 or 64); rows above spill to device memory; 0 = default */
-    int32_t workers_per_cu;  /* batched: resident window workgroups per compute unit; 0 = as many
-                                as LDS allows */
-    int32_t lpt_order;       /* batched: 1 = longest reads first, 0 = input order; -1 = default */
+    int32_t workers_per_cu;  /* batched: window workgroups per compute unit at most; 0 = row tables:
+                                as many as stay resident together (registers and LDS), one pair
+                                per lane: as many as the pairs take. A batch of few pairs has a
+                                workgroup per pair whatever this says */
+    int32_t lpt_order;       /* batched: 1 = longest reads first, 0 = input order; -1 = default
+                                (a batch of few pairs runs all at once) */
     int32_t hard_row;        /* batched: pairs whose start search needs this many edit rows or
                                 more (decoy-like pairs, whose windows cost several DC passes)
                                 go to a separate queue that the window workers drain first;
@@ -252,7 +255,8 @@ int genasm_batch_align_dev(genasm_ctx* ctx, const uint8_t* d_reads2b, const uint
  * holds on every device it runs on until the process ends; the call allocates
  * nothing (no hipMalloc, hipFree or allocating library routine) and does not
  * pin the context. With workers_per_cu = 0 the batched form runs the largest
- * resident window-worker count whose spill fits the array beside the batch.
+ * resident window-worker count whose spill fits the array beside the batch (what
+ * fits is counted so whichever kernels the batch takes, see GENASM_FORM_BATCHED).
  * The bit planes take about (total_read_bases + total_ref_bases) / 4 bytes;
  * the batched form adds about 40 bytes per pair and 0.3 bytes per reference
  * base, plus the spill of its window workers (16 KB each at W = 64, O = 24

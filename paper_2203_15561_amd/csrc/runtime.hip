@@ -391,16 +391,30 @@ constexpr uint32_t kWaveOwnCols = 2048 * 64;
 // Whether such a launch takes one pair per wavefront, the plain form's kernel:
 // up to eight wavefronts per CU. Its windows cost a third to nearly all of a
 // lane's (wave_pair.h) as long as few wavefronts share a SIMD, and there is one
-// launch instead of seven: 4 reads of 150 bases take 15 us against 50, 1,000 of
-// 100 16 against 47, 67 of 30 kb 1.3 ms against 3.9, 2,000 of 3 kb 350 us against
-// 450 (with 30% unrelated pairs 454 against 450), 4,000 of 3 kb 457 against 449
-// (684 against 456). Short reads, whose seven launches take longer than their
-// windows, go there up to twice as many: 4,000 of 250 44 us against 78, 8,000 of
-// 100 78 against 65. Its start search has 64 parts whatever the reference (chunks
-// beyond kWaveOwnCols), so much longer references than reads go to the other path.
-bool wave_path(const genasm_ctx* ctx, uint64_t n_pairs, uint64_t total_ref_bases) {
+// launch instead of seven: 4 reads of 150 bases take 14 us against 50, 1,000 of
+// 100 15 against 47, 67 of 30 kb 1.3 ms against 3.8 (2.4 to 3.1 ms where the search
+// of one of them hits in the wrong place and its windows are of unrelated bases),
+// 2,000 of 3 kb 353 us against 443 (with 30% unrelated pairs 460 against 445), 4,000
+// of 3 kb 457 against 444 (684 against 449). Short reads, whose seven launches take
+// longer than their windows, go there up to twice as many: 4,000 of 250 46 us against
+// 77, 8,000 of 100 78 against 61. Its start search has 64 parts whatever the reference
+// (chunks beyond kWaveOwnCols), so much longer references than reads go to the other
+// path.
+//
+// Small windows cost a wavefront less and a lane, which computes 64 columns whatever
+// the window, the same 5 us: with W of 2 to 8 a wavefront takes 0.3 to 0.8 us a window
+// and the row tables 2.6 to 3.3, so up to four batches of 24 wavefronts a CU go there
+// (6,000 pairs of 2.5 kb, W 2, O 1, k 1: 1.1 ms against 9.9 on lanes and 5.9 on the
+// row tables; 24,000 uneven ones of about 600 bases, W 8, O 7, k 3: 8.5 ms against 25
+// and 22; 24,000 of 600, W 4, O 2: 2.5 ms against 1.7 and 4.0, but uneven 6.0 against
+// 13 and 12). With W up to 16, and up to 32 where k stops it at three levels, eight
+// wavefronts a SIMD are still the fastest or level (8,192 of 3 kb, W 16, O 8: 1.3 ms
+// against 2.1 and 2.3; W 32, O 31, k 3: 1.5 against 10 and 8.4; unrelated pairs of 600
+// bases, W 16, O 8: 0.50 against 0.46).
+bool wave_path(const genasm_ctx* ctx, uint64_t n_pairs, uint64_t total_ref_bases, int W, int K) {
     const uint64_t mean = total_ref_bases / n_pairs;
-    return n_pairs <= (uint64_t)ctx->num_cus * (mean <= 512 ? 16 : 8) && mean <= 65536;
+    const int per_cu = W <= 8 ? 96 : W <= 16 || (W <= 32 && K <= 3) ? 32 : mean <= 512 ? 16 : 8;
+    return n_pairs <= (uint64_t)ctx->num_cus * per_cu && mean <= 65536;
 }
 
 // Whether it takes one pair per lane (lanes.h) otherwise: when its windows commit
@@ -444,8 +458,8 @@ int align_lanes(genasm_ctx* ctx, AlignParams p, const genasm_launch& L, uint64_t
     // short references have larger chunks, since the chunks' lanes look for their
     // reference whether there are long ones or not (100,000 pairs of 250 bases: 173.9
     // us with 28,000 such lanes, 172.9 with 7,000; 172.6 without), and long ones small
-    // chunks, of which they have more (50,000 uneven pairs: 3834 us with 4,096
-    // columns, 3672 with 1,024).
+    // chunks, of which they have more (50,000 uneven pairs: 3.4% faster with 1,024
+    // columns than with 4,096).
     p.search_tail_log = mean <= 512 && total_ref_bases > 16ull << 20 ? 12 : 10;
     const uint64_t chunk = 1ull << p.search_tail_log;
     p.search_part_cols = (uint32_t)std::min<uint64_t>(1u << 30, align_up(std::max(chunk, 2 * mean >> p.search_parts_log), 64));
@@ -683,7 +697,7 @@ int align_dev(genasm_ctx* ctx, const uint8_t* d_reads2b, const uint64_t* d_read_
     // more resident search workgroups than 8 per CU make smaller chunks (each
     // rescanning m1 + 64 columns past its end) and measured slower
     const int search_blocks = ctx->num_cus * L.search_per_cu;
-    const bool waves = default_geometry(L) && wave_path(ctx, n_pairs, total_ref_bases);
+    const bool waves = default_geometry(L) && wave_path(ctx, n_pairs, total_ref_bases, p.W, p.K);
     const bool lanes = default_geometry(L) && !waves && lane_path(p.L);
     const int spill_rows = p.compact ? kCompactSpillRows : 64 - L.lds_rows;
     // Search chunks: at least kBatchSearchChunk columns, and large enough that

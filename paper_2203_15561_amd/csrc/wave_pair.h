@@ -420,7 +420,7 @@ __device__ __forceinline__ int wave_solve(u64 pl, u64 ph, u64 tl, u64 th, int mw
 // long as the rest together, so a pair's own lanes search no more than its first
 // search_own columns, and the chunks after those get lanes of their own: 2,000 reads of 100 bases, one of them with a reference of 10 Mb, took 9.76
 // ms (100,000 of 250: 488 ms) when its pair's lanes searched all of it, against
-// 0.42 (2.04) by chunks of 4,096 columns on the row tables, and 0.15 (0.26) so.
+// 0.42 (2.04) by chunks of 4,096 columns on the row tables, and 0.15 (0.38) so.
 //
 // The chunks' lanes need no list. With chunks of C columns, lane x stands at base
 // (x + 1) C of the batch's references; a reference of n columns holds at least

@@ -255,6 +255,42 @@ def test_rounds_of_one_window():
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("W,O,k", [(2, 1, 1), (2, 0, 2), (4, 2, 4), (8, 7, 3), (8, 3, 8), (16, 8, 16), (32, 31, 3)])
+def test_small_windows_no_slower_than_row_tables(W, O, k):
+    # 6,000 even pairs and 6,000 uneven ones: results and times against the row tables
+    import torch
+
+    def times(ctx, args, kw, launch):
+        best = []
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            ctx.align_dev(*args, launch=launch, **kw)
+            b.record()
+            b.synchronize()
+            best.append(a.elapsed_time(b))
+        return min(best)
+
+    rng = np.random.default_rng(W * 100 + O)
+    for spread in (0.0, 1.0):
+        lens = np.clip(300 * np.exp(spread * rng.normal(0, 1, 6000)), 1, 2400).astype(int)
+        ref_off = np.concatenate([[0], np.cumsum(lens + 20)])
+        read_off = np.concatenate([[0], np.cumsum(lens)])
+        refs = rng.integers(0, 4, ref_off[-1]).astype(np.uint8)
+        reads = np.concatenate([refs[a + 10:a + 10 + m] for a, m in zip(ref_off, lens)])
+        reads = np.where(rng.random(len(reads)) < 0.02, rng.integers(0, 4, len(reads)), reads).astype(np.uint8)
+        args = [torch.from_numpy(x).cuda() for x in (emu.pack2b(reads), read_off, emu.pack2b(refs), ref_off)] + [k, W, O]
+        outs = [torch.zeros((6000, 32), dtype=torch.uint8, device="cuda") for _ in range(2)]
+        cigs = [torch.zeros(len(reads) + len(refs), dtype=torch.int32, device="cuda") for _ in range(2)]
+        kws = [dict(out=o, cigar=c, total_read_bases=len(reads), total_ref_bases=len(refs)) for o, c in zip(outs, cigs)]
+        with ga.Context(0) as ctx:
+            here = times(ctx, args, kws[0], None)
+            tables = times(ctx, args, kws[1], ga.make_launch(ga.FORM_BATCHED, search_per_cu=9))
+        assert torch.equal(outs[0], outs[1]) and torch.equal(cigs[0], cigs[1])
+        assert here < 1.1 * tables, (spread, here, tables)
+
+
+@pytest.mark.gpu
 def test_profile_of_every_path():
     # one pair per wavefront (plain, and a batch of few pairs), one pair per lane with
     # the longest pairs on wavefronts: every pair's cycles and clocks, the workgroups
