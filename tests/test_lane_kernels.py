@@ -114,13 +114,14 @@ def test_batches_emulated(driver, debug_driver, W, O, k):
 
 
 @pytest.mark.slow
-@pytest.mark.parametrize("slots,admit", [(3, 2), (60, 60)])
+@pytest.mark.parametrize("slots,admit", [(3, 2), (20, 20), (60, 60)])
 @pytest.mark.parametrize("budget,ticks", [(0, 40), (2, 0)])
 def test_serving_emulated(driver, slots, admit, budget, ticks):
-    # few resident pairs, a wavefront each (up to two a workgroup), and more, a lane
-    # each; turns that end by time and by windows
-    reads, refs = mixed_batch(60 if slots > 3 else 14, 52, 300)
-    for k, W, O in ((64, 64, 24), (5, 16, 8)):
+    # few resident pairs, a wavefront each (up to two a workgroup; with small windows
+    # up to sixteen, one after the other), and more, a lane each; turns that end by
+    # time and by windows
+    reads, refs = mixed_batch(min(slots, 40) + 11, 52, 300)
+    for k, W, O in ((64, 64, 24), (5, 16, 8), (8, 8, 3)):
         ps = gen.from_lists("serve", reads, refs, k, W, O)
         got = results(*emu.run(driver, ps, emu.SERVE_LANES, window_blocks=2, slots=slots, admit_per_iteration=admit,
                                window_budget=budget, ticks=ticks, search_chunk=64))
@@ -252,6 +253,29 @@ def test_rounds_of_one_window():
             got = results(*ctx.align(reads, refs, 64, launch=launch))
             bad = [i for i in range(len(reads)) if got[i] != want[i]]
             assert not bad, (lpt, len(bad), bad[:5], got[bad[0]], want[bad[0]])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("W,O", [(8, 3), (2, 0), (9, 3)])
+def test_serving_small_windows(W, O):
+    # more resident pairs than wavefronts, and than eight times as many
+    reads, refs = mixed_batch(10_000, 95, 700)
+    ps = gen.from_lists("serve", reads, refs, W, W, O)
+    want = expected_of(ps)
+    with ga.Context(0) as ctx, ga.Server(ctx, W, W, O, cigar_runs=1, max_pending=10_001) as srv:
+        for n in (1500, 10_000):
+            rc, taken = srv.submit_batch(ga.pack(ps.reads), ps.read_off[:n + 1].astype(np.uint64), ga.pack(ps.refs),
+                                         ps.ref_off[:n + 1].astype(np.uint64), np.arange(n, dtype=np.uint64))
+            assert rc == 0 and taken == n
+            done = 0
+            while done < n:
+                info, elems = srv.poll_arrays(timeout_ms=1000)
+                for i in info:
+                    r, at = i["result"], int(i["result"]["cigar_off"])
+                    cigar = ga.decode_cigar(elems[at:at + int(r["cigar_len"])])
+                    assert (int(r["edit_distance"]), cigar, int(r["ref_begin"]), int(r["ref_end"]),
+                            int(r["n_windows"])) == want[int(i["tag"])], int(i["tag"])
+                done += len(info)
 
 
 @pytest.mark.gpu
