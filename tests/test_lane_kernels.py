@@ -242,6 +242,35 @@ def test_long_references(n):
 
 
 @pytest.mark.gpu
+def test_long_reference_first_seen_in_capture():
+    # the slots for long references can't be allocated then: the same results without
+    import torch
+
+    reads, refs = long_references(500, 83, [300_000, 140_000], [7, 400])
+    ps = gen.from_lists("long", reads, refs, 20)
+    want = [(w[0], w[2], w[3]) for w in expected_of(ps)]
+    r, f = torch.from_numpy(emu.pack2b(ps.reads)).cuda(), torch.from_numpy(emu.pack2b(ps.refs)).cuda()
+    ro, fo = (torch.from_numpy(x.astype(np.int64)).cuda() for x in (ps.read_off, ps.ref_off))
+    nr, nf = len(ps.reads), len(ps.refs)
+    out = torch.zeros((500, 32), dtype=torch.uint8, device="cuda")
+    cig = torch.zeros(nr + nf, dtype=torch.int32, device="cuda")
+    with ga.Context(0) as ctx:
+        ctx.align(reads[:3], refs[:3], 20)
+        stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            ctx.align_dev(r, ro, f, fo, 20, out=out, cigar=cig, total_read_bases=nr, total_ref_bases=nf,
+                          stream=stream.cuda_stream)
+        for _ in range(2):
+            out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            got = out.cpu().numpy().reshape(-1).view(ga.RESULT_DTYPE)
+            assert [(int(g["edit_distance"]), int(g["ref_begin"]), int(g["ref_end"])) for g in got] == want
+        del graph
+        ctx.unpin()
+
+
+@pytest.mark.gpu
 def test_rounds_of_one_window():
     # one workgroup a compute unit: 40,000 pairs are three rounds and more
     reads, refs = rounds_of_pairs(40_000, 73)
