@@ -45,7 +45,7 @@ __device__ __forceinline__ void append_run(RunOut& r, int op, uint32_t len) {
 // unrelated pairs in the batch, and every branch costs it more than the few
 // instructions behind it: masks instead (20,000 pairs of 10 kb, 30% of them
 // unrelated: 15,800 -> 8,300 cycles a window, where the other wavefront takes
-// 11,600).
+// 12,600).
 __device__ __forceinline__ void append_path(u64 ins, u64 sub, u64 del, int j, int i, RunOut& r) {
     constexpr int kDelOrIns = (int)GENASM_OP_MISMATCH;
     static_assert(GENASM_OP_INS == kDelOrIns + 1 && GENASM_OP_DEL == kDelOrIns + 2, "ops in order");
@@ -503,7 +503,7 @@ __device__ __forceinline__ void release_roles(const AlignParams& P, const uint32
 // one computes the windows, the other turns each window's path into CIGAR runs
 // while the next window is computed.
 //
-// A lane's window takes 5 us (11,600 cycles: about 2,500 instructions, of which
+// A lane's window takes 5.2 us (12,600 cycles: about 2,500 instructions, of which
 // one wavefront of a SIMD issues one per 4.5 cycles, so their number bounds it)
 // and a batch as long as its longest pair. The first workgroups
 // therefore take the longest pairs a wavefront each, if the lengths are uneven
