@@ -67,7 +67,7 @@ def missing_waits(asm):
     return bad
 
 
-def test_checker_sees_missing_waits():
+def test_planted_missing_waits_are_seen():
     near = "k:\n\tv_cmp_eq_u64_e32 vcc, 0, v[2:3]\n{}\tv_addc_co_u32_e32 v4, vcc, v4, v4, vcc\n"
     lane = "k:\n\tv_add_u32_e32 v1, v2, v3\n{}\tv_readlane_b32 s4, v1, s5\n"
     move = "k:\n\tv_add_u32_e32 v1, v2, v3\n{}\tv_mov_b32_dpp v4, v1 row_shr:1 row_mask:0xf bank_mask:0xf\n"
