@@ -486,9 +486,9 @@ __device__ __forceinline__ bool tail_last(const AlignParams& P, uint64_t first, 
         last = atomicAdd(&slot->done, (u64)parts) + parts == all;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         if (last) {
-            best = atomicMax(&slot->best, 0ull);
-            slot->best = 0ull;
-            slot->done = 0ull;
+            // (given back by atomics too: other slots of the line are in use meanwhile)
+            best = atomicMin(&slot->best, 0ull);
+            atomicAdd(&slot->done, 0ull - all);
         }
     }
     if (!uniform(last)) return false;
